@@ -438,13 +438,15 @@ int lqcd_gauge_force(const lqcd_geom *g, const void *U64, double beta, double c1
                      int32_t accumulate, void *F, void *stream);
 
 /*
- * The same force through staple fields (Sec. 4.3: the staples of 1x1 and 1x2
- * rectangles are the gauge force's building blocks).  For each pair of
- * directions the plaquette staples P+ / P- of every link are stored in the
- * workspace, and each rectangle staple is then two products of those fields
- * and single links (about 51 SU(3) products per link instead of 85).
- * ws must hold lqcd_gauge_force_staples_workspace_bytes(g) bytes (four FP64
- * 18-real link planes: 576 B per site) and not alias U64 or F.  Equal to
+ * The same force through stored loops (Sec. 4.3: the 1x1 and 1x2 rectangles
+ * are the gauge force's building blocks).  For each plane of directions the
+ * traceless anti-Hermitian parts of the plaquette and of the two rectangles
+ * at every site are stored in the workspace, and each staple of a link is
+ * then one of those matrices moved along the loop by single links (about 29
+ * SU(3) products per link instead of 85; the links must be unitary).
+ * ws must hold lqcd_gauge_force_staples_workspace_bytes(g) bytes (576 B per
+ * site, three planes at a time) and not alias U64 or F; given twice that, all
+ * six planes are formed at once and F is written once.  Equal to
  * lqcd_gauge_force up to rounding.  Stream-ordered, asynchronous.
  */
 size_t lqcd_gauge_force_staples_workspace_bytes(const lqcd_geom *g);

@@ -699,7 +699,9 @@ def gauge_force(geom: Geometry, U64, beta: float, c1: float = SYMANZIK_C1, out=N
         _check(_fn("lqcd_gauge_force")(geom.c(), _ptr(U64), float(beta), float(c1),
                                        1 if accumulate else 0, _ptr(out), _stream()))
     elif method == "staples":
-        nbytes = int(_fn("lqcd_gauge_force_staples_workspace_bytes")(geom.c()))
+        # twice the required size lets the library form the loops of all six
+        # planes in one pass and write the force once
+        nbytes = 2 * int(_fn("lqcd_gauge_force_staples_workspace_bytes")(geom.c()))
         ws = _workspace(nbytes, U64.device)
         _check(_fn("lqcd_gauge_force_staples")(geom.c(), _ptr(U64), float(beta), float(c1),
                                                1 if accumulate else 0, _ptr(out), _ptr(ws),

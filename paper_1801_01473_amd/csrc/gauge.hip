@@ -19,7 +19,8 @@
 
 #include <cmath>
 
-#include "common.h"
+#include "gauge.h"
+#include "m3.h"
 #include "tile.h"
 
 namespace lqcd {
@@ -28,113 +29,6 @@ namespace {
 
 constexpr int kGaugeBlock = 128;
 constexpr int kMdBlock = 256;
-
-struct M3 {
-  double2 e[9];
-};
-
-__device__ __forceinline__ M3 m_zero() {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 9; ++i) r.e[i] = make_double2(0.0, 0.0);
-  return r;
-}
-
-__device__ __forceinline__ M3 m_unit() {
-  M3 r = m_zero();
-  r.e[0].x = r.e[4].x = r.e[8].x = 1.0;
-  return r;
-}
-
-// a b, a b^dag, a^dag b
-__device__ __forceinline__ M3 m_mul(const M3& a, const M3& b) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = cmul<double>(a.e[3 * i], b.e[j]);
-      cfma<double>(s, a.e[3 * i + 1], b.e[3 + j]);
-      cfma<double>(s, a.e[3 * i + 2], b.e[6 + j]);
-      r.e[3 * i + j] = s;
-    }
-  return r;
-}
-
-__device__ __forceinline__ M3 m_mul_dag(const M3& a, const M3& b) {
-  M3 r;  // r_ij = sum_k a_ik conj(b_jk)
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = cmulc<double>(b.e[3 * j], a.e[3 * i]);
-      cfmac<double>(s, b.e[3 * j + 1], a.e[3 * i + 1]);
-      cfmac<double>(s, b.e[3 * j + 2], a.e[3 * i + 2]);
-      r.e[3 * i + j] = s;
-    }
-  return r;
-}
-
-__device__ __forceinline__ M3 m_dag_mul(const M3& a, const M3& b) {
-  M3 r;  // r_ij = sum_k conj(a_ki) b_kj
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = cmulc<double>(a.e[i], b.e[j]);
-      cfmac<double>(s, a.e[3 + i], b.e[3 + j]);
-      cfmac<double>(s, a.e[6 + i], b.e[6 + j]);
-      r.e[3 * i + j] = s;
-    }
-  return r;
-}
-
-__device__ __forceinline__ void m_axpy(double w, const M3& a, M3& acc) {
-#pragma unroll
-  for (int i = 0; i < 9; ++i) {
-    acc.e[i].x = fma(w, a.e[i].x, acc.e[i].x);
-    acc.e[i].y = fma(w, a.e[i].y, acc.e[i].y);
-  }
-}
-
-__device__ __forceinline__ double re_tr(const M3& a) { return a.e[0].x + a.e[4].x + a.e[8].x; }
-
-// Coordinates with periodic wrap (named fields: a direction index chosen at
-// run time selects among them, so nothing is indexed dynamically), and the
-// link U_mu at a site.
-struct C4 {
-  int x, y, z, t;
-};
-
-__device__ __forceinline__ int wrap(int v, int L) { return v < 0 ? v + L : (v >= L ? v - L : v); }
-
-__device__ __forceinline__ C4 shift(const KGeom& g, C4 s, int mu, int d) {
-  if (mu == 0)
-    s.x = wrap(s.x + d, g.Lx);
-  else if (mu == 1)
-    s.y = wrap(s.y + d, g.Ly);
-  else if (mu == 2)
-    s.z = wrap(s.z + d, g.Lz);
-  else
-    s.t = wrap(s.t + d, g.Lt);
-  return s;
-}
-
-__device__ __forceinline__ M3 link(const KGeom& g, const double2* __restrict__ U, const C4& s,
-                                   int mu) {
-  const int par = (s.x + s.y + s.z + s.t) & 1;
-  const int h = (s.x >> 1) + g.Lxh * (s.y + g.Ly * (s.z + g.Lz * s.t));
-  const double2* p = U + (int64_t(par) * 4 + mu) * 9 * int64_t(g.Vh) + h;
-  M3 r;
-#pragma unroll
-  for (int e = 0; e < 9; ++e) r.e[e] = p[int64_t(e) * g.Vh];
-  return r;
-}
-
-__device__ __forceinline__ C4 site_c4(const KGeom& g, int h, int par) {
-  const Site s = decode_site(g, h, par);
-  return C4{s.x, s.y, s.z, s.t};
-}
 
 // Weighted staple sum of the link U_mu(x): Tr[U_mu(x) A] runs over every
 // plaquette (weight c0) and every 1x2 rectangle (weight c1) through the link,
@@ -226,20 +120,6 @@ __device__ M3 staples(const KGeom& g, const double2* __restrict__ U, const C4& x
   return A;
 }
 
-// TA(W) = (W - W^dag)/2 - Tr(W - W^dag)/6
-__device__ __forceinline__ M3 traceless_antiherm(const M3& w) {
-  M3 r;
-  const double tr_im = (w.e[0].y + w.e[4].y + w.e[8].y) / 3.0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const double2 a = w.e[3 * i + j], b = w.e[3 * j + i];
-      r.e[3 * i + j] = make_double2(0.5 * (a.x - b.x), 0.5 * (a.y + b.y) - (i == j ? tr_im : 0.0));
-    }
-  return r;
-}
-
 // One thread per link in the link_thread order (segment = mu; both parities
 // of 64 half indices per workgroup, so each (parity, mu, element) plane is
 // written coalesced); the blocks of one XCD take consecutive chunks, and the
@@ -269,134 +149,6 @@ __global__ void __launch_bounds__(kGaugeBlock) k_gauge_force(KGeom g, const doub
   for (int e = 0; e < 9; ++e) {
     double2 v = f.e[e];
     if (accumulate) {
-      const double2 o = out[int64_t(e) * g.Vh];
-      v.x += o.x;
-      v.y += o.y;
-    }
-    out[int64_t(e) * g.Vh] = v;
-  }
-}
-
-// ---------------------------------------------------------------- staple fields
-// The force through staple fields, one unordered direction pair {mu, nu} at a
-// time.  For a link direction a and another direction b, with the plaquette
-// staples of the link (x, a)
-//   P+_ab(x) = U_b(x+a) U_a(x+b)^dag U_b(x)^dag,
-//   P-_ab(x) = U_b(x+a-b)^dag U_a(x-b)^dag U_b(x-b),
-// each 2x1 / 1x2 rectangle staple of (x, a) is two products of these fields
-// and single links (inserting U U^dag = 1 along the loop):
-//   2x1, link first, up:   U_a(x+a) P+_ab(x+a) P+_ab(x)
-//   2x1, link second, up:  P+_ab(x) U_b(x) P-_ba(x)
-//   2x1, link first, down: U_a(x+a) P-_ab(x+a) P-_ab(x)
-//   2x1, link second, down: P-_ab(x) U_b(x-b)^dag P-_ba(x-b)^dag
-//   1x2, up:               U_b(x+a) P+_ab(x+b) U_b(x)^dag
-//   1x2, down:             U_b(x+a-b)^dag P-_ab(x-b) U_b(x-b)
-// Pass 1 stores P+_mu,nu, P-_mu,nu, P+_nu,mu, P-_nu,mu for every site (fields
-// 0..3, each packed like one direction of the links: [parity][9][Vh]); pass 2
-// forms, for the links of both directions, A_ab = c0 (P+ + P-) + c1 (the six
-// rectangles) and adds -(beta/3) TA(U_a A_ab) to F_a.  Per link that is about
-// 51 SU(3) products over the six pairs, against 85 for the direct sum.
-
-__device__ __forceinline__ M3 sfield(const KGeom& g, const double2* __restrict__ P, int f,
-                                     const C4& s) {
-  const int par = (s.x + s.y + s.z + s.t) & 1;
-  const int h = (s.x >> 1) + g.Lxh * (s.y + g.Ly * (s.z + g.Lz * s.t));
-  const double2* p = P + (int64_t(f) * 2 + par) * 9 * int64_t(g.Vh) + h;
-  M3 r;
-#pragma unroll
-  for (int e = 0; e < 9; ++e) r.e[e] = p[int64_t(e) * g.Vh];
-  return r;
-}
-
-// pass 1: one thread per site (the link_thread order with one segment; sites
-// in the z-slab order of k_gauge_force, blocks XCD-contiguous)
-__global__ void __launch_bounds__(kGaugeBlock) k_staple_fields(KGeom g,
-                                                               const double2* __restrict__ U,
-                                                               int mu, int nu, int tz,
-                                                               double2* P) {
-  LinkThread lt;
-  if (!link_thread(g, int64_t(xcd_block(blockIdx.x, gridDim.x, 1)) * blockDim.x + threadIdx.x,
-                   lt))
-    return;
-  const int par = lt.par, h = tiled_half_index(g, lt.i, g.Ly, tz);
-  const C4 x = site_c4(g, h, par);
-#pragma unroll 1
-  for (int f = 0; f < 4; ++f) {
-    const int a = f < 2 ? mu : nu, b = f < 2 ? nu : mu;
-    M3 t;
-    if ((f & 1) == 0) {  // P+_ab(x) = U_b(x+a) U_a(x+b)^dag U_b(x)^dag
-      t = m_mul_dag(link(g, U, shift(g, x, a, 1), b), link(g, U, shift(g, x, b, 1), a));
-      t = m_mul_dag(t, link(g, U, x, b));
-    } else {  // P-_ab(x) = U_b(x+a-b)^dag U_a(x-b)^dag U_b(x-b)
-      const C4 xm = shift(g, x, b, -1);
-      t = m_dag_mul(link(g, U, shift(g, xm, a, 1), b),
-                    m_dag_mul(link(g, U, xm, a), link(g, U, xm, b)));
-    }
-    double2* out = P + (int64_t(f) * 2 + par) * 9 * int64_t(g.Vh) + h;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) out[int64_t(e) * g.Vh] = t.e[e];
-  }
-}
-
-// pass 2: one thread per link of the two directions (the link_thread order,
-// segment = side; side 0: a = mu, side 1: a = nu; sites in the z-slab order,
-// blocks XCD-contiguous).  first_mask bit side: write F_a instead of adding
-// to it.
-__global__ void __launch_bounds__(kGaugeBlock) k_force_pair(KGeom g, const double2* __restrict__ U,
-                                                            const double2* __restrict__ P,
-                                                            int mu, int nu, double beta,
-                                                            double c0, double c1, int first_mask,
-                                                            int tz, double2* F) {
-  LinkThread lt;
-  if (!link_thread(g, int64_t(xcd_block(blockIdx.x, gridDim.x, 1)) * blockDim.x + threadIdx.x,
-                   lt))
-    return;
-  const int h = tiled_half_index(g, lt.i, g.Ly, tz);
-  const int side = lt.seg, par = lt.par;
-  const int a = side ? nu : mu, b = side ? mu : nu;
-  const int fp = side ? 2 : 0, fm = side ? 3 : 1, fmo = side ? 1 : 3;  // P+_ab, P-_ab, P-_ba
-  const C4 x = site_c4(g, h, par);
-  const C4 xa = shift(g, x, a, 1), xb = shift(g, x, b, 1), xmb = shift(g, x, b, -1);
-  // Terms in an order that retires each field soon after its last use; the
-  // links and fields used twice are loaded again (cache hits) rather than
-  // held.  (Scheduling barriers between the terms halve the registers, 184
-  // against 256 + 106 AGPRs, but serialise the terms' loads: 36.1 against
-  // 33.2 ms at 48^4, so the compiler's hoisting is kept.)
-  M3 A = m_zero();
-  {
-    const M3 pp = sfield(g, P, fp, x);
-    m_axpy(c0, pp, A);
-    if (c1 != 0.0) {
-      m_axpy(c1, m_mul(m_mul(link(g, U, xa, a), sfield(g, P, fp, xa)), pp), A);
-      m_axpy(c1, m_mul(m_mul(pp, link(g, U, x, b)), sfield(g, P, fmo, x)), A);
-    }
-  }
-  {
-    const M3 pm = sfield(g, P, fm, x);
-    m_axpy(c0, pm, A);
-    if (c1 != 0.0) {
-      m_axpy(c1, m_mul(m_mul(link(g, U, xa, a), sfield(g, P, fm, xa)), pm), A);
-      m_axpy(c1, m_mul_dag(m_mul_dag(pm, link(g, U, xmb, b)), sfield(g, P, fmo, xmb)), A);
-    }
-  }
-  if (c1 != 0.0) {
-    m_axpy(c1, m_mul_dag(m_mul(link(g, U, xa, b), sfield(g, P, fp, xb)), link(g, U, x, b)), A);
-    m_axpy(c1,
-           m_mul(m_dag_mul(link(g, U, shift(g, xa, b, -1), b), sfield(g, P, fm, xmb)),
-                 link(g, U, xmb, b)),
-           A);
-  }
-  M3 W = m_mul(link(g, U, x, a), A);
-  const double s = -beta / 3.0;
-#pragma unroll
-  for (int e = 0; e < 9; ++e) W.e[e] = make_double2(s * W.e[e].x, s * W.e[e].y);
-  const M3 f = traceless_antiherm(W);
-  double2* out = F + (int64_t(par) * 4 + a) * 9 * g.Vh + h;
-  const bool first = (first_mask >> side) & 1;
-#pragma unroll
-  for (int e = 0; e < 9; ++e) {
-    double2 v = f.e[e];
-    if (!first) {
       const double2 o = out[int64_t(e) * g.Vh];
       v.x += o.x;
       v.y += o.y;
@@ -782,6 +534,31 @@ int reduce_to_host(const double* part, int nb, double scale, double* out_dev, do
 
 }  // namespace
 
+int gauge_force_direct(const KGeom& k, const double2* U, double beta, double c1, int accumulate,
+                       double2* F, hipStream_t s) {
+  const int64_t n = 4 * link_threads_per_segment(k.Vh);
+  // F is linear in the staple sum, so the shapes split over three launches:
+  // the later ones add TA(U (-beta/3) A_k) onto the first's result.
+  const dim3 grid(unsigned(n / kGaugeBlock));
+  const int tz = slab_tile(k.Lz);
+  if (c1 == 0.0) {
+    hipLaunchKernelGGL(k_gauge_force<kStaplePlaq>, grid, dim3(kGaugeBlock), 0, s, k, U, beta, 1.0,
+                       0.0, accumulate, tz, F);
+    LQCD_LAUNCH_CHECK();
+    return LQCD_OK;
+  }
+  hipLaunchKernelGGL(k_gauge_force<kStaplePass1>, grid, dim3(kGaugeBlock), 0, s, k, U, beta,
+                     1.0 - 8.0 * c1, c1, accumulate, tz, F);
+  LQCD_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_gauge_force<kStaplePass2>, grid, dim3(kGaugeBlock), 0, s, k, U, beta,
+                     1.0 - 8.0 * c1, c1, 1, tz, F);
+  LQCD_LAUNCH_CHECK();
+  hipLaunchKernelGGL(k_gauge_force<kStaplePass3>, grid, dim3(kGaugeBlock), 0, s, k, U, beta,
+                     1.0 - 8.0 * c1, c1, 1, tz, F);
+  LQCD_LAUNCH_CHECK();
+  return LQCD_OK;
+}
+
 }  // namespace lqcd
 
 using namespace lqcd;
@@ -922,81 +699,8 @@ int lqcd_gauge_force(const lqcd_geom* g, const void* U64, double beta, double c1
     set_error("F must not alias U64");
     return LQCD_ERR_INVALID_ARG;
   }
-  const KGeom k = make_kgeom(g);
-  const int64_t n = 4 * link_threads_per_segment(k.Vh);
-  // F is linear in the staple sum, so the shapes split over three launches:
-  // the later ones add TA(U (-beta/3) A_k) onto the first's result.
-  const dim3 grid(unsigned(n / kGaugeBlock));
-  const hipStream_t s = (hipStream_t)stream;
-  const int tz = slab_tile(k.Lz);
-  if (c1 == 0.0) {
-    hipLaunchKernelGGL(k_gauge_force<kStaplePlaq>, grid, dim3(kGaugeBlock), 0, s, k,
-                       (const double2*)U64, beta, 1.0, 0.0, accumulate, tz, (double2*)F);
-    LQCD_LAUNCH_CHECK();
-    return LQCD_OK;
-  }
-  hipLaunchKernelGGL(k_gauge_force<kStaplePass1>, grid, dim3(kGaugeBlock), 0, s, k,
-                     (const double2*)U64, beta, 1.0 - 8.0 * c1, c1, accumulate, tz, (double2*)F);
-  LQCD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_gauge_force<kStaplePass2>, grid, dim3(kGaugeBlock), 0, s, k,
-                     (const double2*)U64, beta, 1.0 - 8.0 * c1, c1, 1, tz, (double2*)F);
-  LQCD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_gauge_force<kStaplePass3>, grid, dim3(kGaugeBlock), 0, s, k,
-                     (const double2*)U64, beta, 1.0 - 8.0 * c1, c1, 1, tz, (double2*)F);
-  LQCD_LAUNCH_CHECK();
-  return LQCD_OK;
-}
-
-size_t lqcd_gauge_force_staples_workspace_bytes(const lqcd_geom* g) {
-  if (check_geom(g)) return 0;
-  const KGeom k = make_kgeom(g);
-  return size_t(4) * 2 * 9 * size_t(k.Vh) * sizeof(double2);
-}
-
-int lqcd_gauge_force_staples(const lqcd_geom* g, const void* U64, double beta, double c1,
-                             int32_t accumulate, void* F, void* ws, size_t ws_bytes,
-                             void* stream) {
-  clear_error();
-  int rc;
-  if ((rc = check_geom(g)) || (rc = check_ptr(U64, "U64")) || (rc = check_ptr(F, "F")) ||
-      (rc = check_ptr(ws, "ws")) || (rc = check_c1(beta, c1)))
-    return rc;
-  if (accumulate != 0 && accumulate != 1) {
-    set_error("accumulate must be 0 or 1");
-    return LQCD_ERR_INVALID_ARG;
-  }
-  if (F == U64 || ws == U64 || ws == F) {
-    set_error("F, U64 and ws must be distinct buffers");
-    return LQCD_ERR_INVALID_ARG;
-  }
-  const size_t need = lqcd_gauge_force_staples_workspace_bytes(g);
-  if (ws_bytes < need) {
-    set_error("gauge force workspace of %zu bytes is too small: %zu needed", ws_bytes, need);
-    return LQCD_ERR_WORKSPACE;
-  }
-  const KGeom k = make_kgeom(g);
-  const hipStream_t s = (hipStream_t)stream;
-  const dim3 g1(unsigned(link_threads_per_segment(k.Vh) / kGaugeBlock));
-  const dim3 g2(unsigned(2 * link_threads_per_segment(k.Vh) / kGaugeBlock));
-  const int tz = slab_tile(k.Lz);
-  int seen = 0;  // directions whose F has been written
-  for (int mu = 0; mu < 4; ++mu)
-    for (int nu = mu + 1; nu < 4; ++nu) {
-      int first = 0;
-      if (!accumulate) {
-        if (!(seen & (1 << mu))) first |= 1;
-        if (!(seen & (1 << nu))) first |= 2;
-      }
-      seen |= (1 << mu) | (1 << nu);
-      hipLaunchKernelGGL(k_staple_fields, g1, dim3(kGaugeBlock), 0, s, k, (const double2*)U64,
-                         mu, nu, tz, (double2*)ws);
-      LQCD_LAUNCH_CHECK();
-      hipLaunchKernelGGL(k_force_pair, g2, dim3(kGaugeBlock), 0, s, k, (const double2*)U64,
-                         (const double2*)ws, mu, nu, beta, 1.0 - 8.0 * c1, c1, first, tz,
-                         (double2*)F);
-      LQCD_LAUNCH_CHECK();
-    }
-  return LQCD_OK;
+  return gauge_force_direct(make_kgeom(g), (const double2*)U64, beta, c1, accumulate,
+                            (double2*)F, (hipStream_t)stream);
 }
 
 int lqcd_md_update_momenta(const lqcd_geom* g, const void* F, double eps, void* H,

@@ -1,0 +1,385 @@
+// The Symanzik gauge force through loop fields (Sec. 4.3: the 1x1 and 1x2
+// rectangles are the building blocks of the gauge force).
+//
+// For a plane of directions a < b and a site x, with the links of that plane,
+//   l(x)  the plaquette        a, b, -a, -b
+//   ra(x) the 2x1 rectangle    a, a, b, -a, -a, -b
+//   rb(x) the 1x2 rectangle    a, b, b, -a, -b, -b
+// closed loops at x, of which only the traceless anti-Hermitian part TA is
+// needed: F_a(x) = -(beta/3) sum of w TA(loop at x that starts along a) over
+// the loops through the link (x, a), and TA commutes with moving a loop's
+// base point, TA(V^dag W V) = V^dag TA(W) V for unitary V.  Every loop through
+// (x, a) is one of l, ra, rb based at x, x-a, x-b, x-2b or x-a-b, moved to x
+// along its own links, reversed (sign -) where (x, a) is its upper side:
+//   F_a/(-beta/3) = c0 l(x) + c1 (ra(x) + rb(x))
+//     - Ub(x-b)^dag [ c0 l(x-b) + c1 ra(x-b) + c1 Ub(x-2b)^dag rb(x-2b) Ub(x-2b) ] Ub(x-b)
+//     + c1 Ua(x-a)^dag [ ra(x-a) - Ub(x-a-b)^dag ra(x-a-b) Ub(x-a-b) ] Ua(x-a)
+// summed over b (the last transport once for the sum).  For b < a the stored
+// loops of the plane (b, a) run the other way round: l -> -l, ra -> -rb,
+// rb -> -ra.
+//
+// Pass 1 (k_loops, one thread per site and plane): 11 SU(3) products; TA of the
+// loops, stored as 8 reals each.  Pass 2 (k_loop_force, one thread per link):
+// 10 transports V^dag A V, about 0.64 of two products each.  That is 66 + 51
+// products per site, against 204 when the plaquette staples of each plane
+// were stored as full matrices and 340 with every staple multiplied out, and
+// 2 launches instead of 12.  Both passes are bound by their memory path, not
+// by arithmetic (with the products taken out of a copy they took the same
+// time): pass 1 by HBM (3.1 GB of links read ~3 times through 4 MB L2s, 6.1 GB
+// written, 3.8 ms at 48^4), pass 2 by the L2-to-L1 traffic, about 12 TB/s, so
+// the links that the waves of a workgroup share go through LDS (4.5 -> 3.7 ms).
+// 48^4: 25.6 ms with stored staples, 7.4 ms now; 32^3 x 48: 2.1 ms.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+
+#include "gauge.h"
+#include "m3.h"
+#include "tile.h"
+
+namespace lqcd {
+
+namespace {
+
+// Traceless anti-Hermitian 3x3 matrix: entries 01, 02, 12 and the imaginary
+// parts of 00 and 11.  Stored as four complex planes.
+struct Alg {
+  double2 o01, o02, o12, d;
+};
+
+__device__ __forceinline__ Alg a_zero() {
+  const double2 z = make_double2(0.0, 0.0);
+  return Alg{z, z, z, z};
+}
+
+__device__ __forceinline__ void a_axpy(double w, const Alg& a, Alg& s) {
+  s.o01 = make_double2(fma(w, a.o01.x, s.o01.x), fma(w, a.o01.y, s.o01.y));
+  s.o02 = make_double2(fma(w, a.o02.x, s.o02.x), fma(w, a.o02.y, s.o02.y));
+  s.o12 = make_double2(fma(w, a.o12.x, s.o12.x), fma(w, a.o12.y, s.o12.y));
+  s.d = make_double2(fma(w, a.d.x, s.d.x), fma(w, a.d.y, s.d.y));
+}
+
+__device__ __forceinline__ double2 anti(const double2 a, const double2 b) {
+  return make_double2(0.5 * (a.x - b.x), 0.5 * (a.y + b.y));
+}
+
+// TA(a b^dag)
+__device__ __forceinline__ Alg ta_mul_dag(const M3& a, const M3& b) {
+  const M3 w = m_mul_dag(a, b);
+  const double tr = (w.e[0].y + w.e[4].y + w.e[8].y) / 3.0;
+  return Alg{anti(w.e[1], w.e[3]), anti(w.e[2], w.e[6]), anti(w.e[5], w.e[7]),
+             make_double2(w.e[0].y - tr, w.e[4].y - tr)};
+}
+
+// U^dag A U
+__device__ __forceinline__ Alg transport(const M3& u, const Alg& a) {
+  const double d2 = -(a.d.x + a.d.y);
+  M3 t;  // A U; row 1 and 2 of A hold -conj of the stored entries
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    double2 s = make_double2(-a.d.x * u.e[j].y, a.d.x * u.e[j].x);
+    cfma<double>(s, a.o01, u.e[3 + j]);
+    cfma<double>(s, a.o02, u.e[6 + j]);
+    t.e[j] = s;
+    s = make_double2(-a.d.y * u.e[3 + j].y, a.d.y * u.e[3 + j].x);
+    cfmac<double>(s, make_double2(-a.o01.x, -a.o01.y), u.e[j]);
+    cfma<double>(s, a.o12, u.e[6 + j]);
+    t.e[3 + j] = s;
+    s = make_double2(-d2 * u.e[6 + j].y, d2 * u.e[6 + j].x);
+    cfmac<double>(s, make_double2(-a.o02.x, -a.o02.y), u.e[j]);
+    cfmac<double>(s, make_double2(-a.o12.x, -a.o12.y), u.e[3 + j]);
+    t.e[6 + j] = s;
+  }
+  auto entry = [&](int i, int j) {
+    double2 s = cmulc<double>(u.e[i], t.e[j]);
+    cfmac<double>(s, u.e[3 + i], t.e[3 + j]);
+    cfmac<double>(s, u.e[6 + i], t.e[6 + j]);
+    return s;
+  };
+  auto diag = [&](int i) {  // imaginary part only
+    double s = fma(u.e[i].x, t.e[i].y, -(u.e[i].y * t.e[i].x));
+    s = fma(u.e[3 + i].x, t.e[3 + i].y, fma(-u.e[3 + i].y, t.e[3 + i].x, s));
+    return fma(u.e[6 + i].x, t.e[6 + i].y, fma(-u.e[6 + i].y, t.e[6 + i].x, s));
+  };
+  return Alg{entry(0, 1), entry(0, 2), entry(1, 2), make_double2(diag(0), diag(1))};
+}
+
+// The planes whose loop fields one pass pair holds: slot s has the fields
+//   0: c0 l + c1 (ra + rb), the sum that both directions take at x itself
+//      (c0 l + c1 ra is that minus c1 rb), -beta/3 included,  1: ra,  2: rb.
+struct Planes {
+  int n;
+  int a[6], b[6];
+  int slot[4][4];  // plane of two directions, -1: not in this pass
+  int dirs;        // bit mu: the pass writes F_mu
+  int add;         // bit mu: add to F_mu instead of writing it
+  int sh;          // log2 of the chunk of half indices
+};
+
+constexpr size_t kPlaneBytes = 3 * 128;  // loop fields of a plane per half index, both parities
+
+// Loop fields are stored by chunks of 2^sh half indices, [chunk][parity][slot]
+// [field][4][2^sh], so that what a wave reads around a site lies in a few
+// contiguous regions instead of one page per plane of the lattice (3 % of the
+// force at 48^4).  The chunk divides Vh (a multiple of 8): the largest of 64,
+// 32, 16, 8, so the fields fill Vh entries exactly.
+inline int chunk_shift(int Vh) {
+  int s = 6;
+  while (Vh & ((1 << s) - 1)) --s;
+  return s;
+}
+
+__device__ __forceinline__ double2* field_at(double2* P, const Planes& pl, int slot, int f,
+                                             int par, int h) {
+  const int64_t c = int64_t(h >> pl.sh) * 2 + par;
+  return P + ((c * (pl.n * 12) + (slot * 3 + f) * 4) << pl.sh) + (h & ((1 << pl.sh) - 1));
+}
+
+__device__ __forceinline__ Alg ld_alg(const double2* __restrict__ P, const Planes& pl, int slot,
+                                      int f, int par, int h) {
+  const double2* p = field_at(const_cast<double2*>(P), pl, slot, f, par, h);
+  const int n = 1 << pl.sh;
+  return Alg{p[0], p[n], p[2 * n], p[3 * n]};
+}
+
+__device__ __forceinline__ void st_alg(double2* __restrict__ P, const Planes& pl, int slot, int f,
+                                       int par, int h, const Alg& a) {
+  double2* p = field_at(P, pl, slot, f, par, h);
+  const int n = 1 << pl.sh;
+  p[0] = a.o01;
+  p[n] = a.o02;
+  p[2 * n] = a.o12;
+  p[3 * n] = a.d;
+}
+
+__device__ __forceinline__ M3 lds_m3(const double2 (&s)[9][64], int lane) {
+  M3 m;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) m.e[e] = s[e][lane];
+  return m;
+}
+
+// a b, with a read from LDS as it is used (no registers held for it)
+__device__ __forceinline__ M3 lds_mul(const double2 (&a)[9][64], int lane, const M3& b) {
+  M3 r;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      double2 s = cmul<double>(a[3 * i][lane], b.e[j]);
+      cfma<double>(s, a[3 * i + 1][lane], b.e[3 + j]);
+      cfma<double>(s, a[3 * i + 2][lane], b.e[6 + j]);
+      r.e[3 * i + j] = s;
+    }
+  return r;
+}
+
+// One workgroup per 64 half indices of one parity, wave = plane.  The links
+// U_mu(x) and U_mu(x + mu), which three planes use (twice each), go through LDS.
+__global__ void __launch_bounds__(384, 3) k_loops(KGeom g, const double2* __restrict__ U,
+                                               const Planes pl, double w0, double w1, int ty,
+                                               int tz, double2* __restrict__ P) {
+  __shared__ double2 sh[2][4][9][64];  // U_mu(x), U_mu(x + mu)
+  const ChunkSite cs = chunk_site(g, ty, tz);
+  const int h = cs.h, par = cs.par, opp = 1 - par, lane = cs.lane, task = cs.task;
+  const C4 x = site_c4(g, h, par);
+  for (int m = task; m < 8; m += pl.n) {
+    const int mu = m & 3, far = m >> 2;
+    const M3 u = ld_m3(link_res(g, U, far ? opp : par, mu),
+                       h + (far ? axis(g, x, mu).off(1) : 0), g.Vh);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) sh[far][mu][e][lane] = u.e[e];
+  }
+  const int a = pl.a[task], b = pl.b[task];
+  const Axis xa = axis(g, x, a), xb = axis(g, x, b);
+  const int a1 = h + xa.off(1), b1 = h + xb.off(1);
+  const int ab = a1 + (b1 - h), a2 = h + xa.off(2), b2 = h + xb.off(2);
+  // links leaving sites of the same and of the other parity
+  const auto a_s = link_res(g, U, par, a), b_s = link_res(g, U, par, b);
+  const auto a_o = link_res(g, U, opp, a), b_o = link_res(g, U, opp, b);
+  __syncthreads();
+  if (!cs.in) return;
+  // (the barriers keep the compiler from loading every section's links at
+  // once: 168 registers without spilling, so two workgroups share a CU)
+  const M3 c1 = lds_mul(sh[0][a], lane, ld_m3(b_o, a1, g.Vh));  // a, b
+  __builtin_amdgcn_sched_barrier(0);
+  const M3 c2 = lds_mul(sh[0][b], lane, ld_m3(a_o, b1, g.Vh));  // b, a
+  Alg sum = a_zero();
+  a_axpy(w0, ta_mul_dag(c1, c2), sum);
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    const M3 r = m_mul(c2, ld_m3(a_s, ab, g.Vh));  // b, a, a
+    const M3 e = lds_mul(sh[1][a], lane, ld_m3(b_s, a2, g.Vh));
+    const M3 l = lds_mul(sh[0][a], lane, e);    // a, a, b
+    const Alg ra = ta_mul_dag(l, r);
+    st_alg(P, pl, task, 1, par, h, ra);
+    a_axpy(w1, ra, sum);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    const M3 l = m_mul(c1, ld_m3(b_s, ab, g.Vh));  // a, b, b
+    const M3 e = lds_mul(sh[1][b], lane, ld_m3(a_s, b2, g.Vh));
+    const M3 r = lds_mul(sh[0][b], lane, e);    // b, b, a
+    const Alg rb = ta_mul_dag(l, r);
+    st_alg(P, pl, task, 2, par, h, rb);
+    a_axpy(w1, rb, sum);
+  }
+  st_alg(P, pl, task, 0, par, h, sum);
+}
+
+// One workgroup per 64 half indices of one parity, wave = direction a.  The
+// links U_mu(x - mu), U_mu(x - 2 mu) of the transports, which three or four
+// waves use, go through LDS: 20 link matrices per site from L2 instead of 40.
+__global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* __restrict__ U,
+                                                       const double2* __restrict__ P,
+                                                       const Planes pl, double w1, int ty,
+                                                       int tz, double2* __restrict__ F) {
+  __shared__ double2 sh[4][2][9][64];  // U_mu(x - mu), U_mu(x - 2 mu)
+  const ChunkSite cs = chunk_site(g, ty, tz);
+  const int h = cs.h, par = cs.par, opp = 1 - par, lane = cs.lane, a = cs.task;
+  const C4 x = site_c4(g, h, par);
+  {
+    const Axis xa = axis(g, x, a);
+    const M3 u1 = ld_m3(link_res(g, U, opp, a), h + xa.off(-1), g.Vh);
+    const M3 u2 = ld_m3(link_res(g, U, par, a), h + xa.off(-2), g.Vh);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      sh[a][0][e][lane] = u1.e[e];
+      sh[a][1][e][lane] = u2.e[e];
+    }
+  }
+  __syncthreads();
+  const int am = axis(g, x, a).off(-1);
+  Alg f = a_zero(), q = a_zero();
+#pragma unroll 1
+  for (int b = 0; b < 4; ++b) {
+    if (b == a) continue;
+    const int s = pl.slot[a][b];
+    if (s < 0) continue;
+    const double sg = a < b ? 1.0 : -1.0;
+    const int fa = a < b ? 1 : 2, fb = 3 - fa;  // fields of ra, rb
+    const Axis xb = axis(g, x, b);
+    const int hb = h + xb.off(-1), h2 = h + xb.off(-2);
+    Alg z = ld_alg(P, pl, s, 0, opp, hb);
+    Alg y = transport(lds_m3(sh[b][1], lane), ld_alg(P, pl, s, fb, par, h2));
+    a_axpy(-1.0, ld_alg(P, pl, s, fb, opp, hb), y);
+    a_axpy(w1, y, z);
+    z = transport(lds_m3(sh[b][0], lane), z);
+    a_axpy(-sg, z, f);
+    a_axpy(sg, ld_alg(P, pl, s, 0, par, h), f);
+    a_axpy(sg, ld_alg(P, pl, s, fa, opp, h + am), q);
+    y = transport(ld_m3(link_res(g, U, par, b), hb + am, g.Vh),
+                  ld_alg(P, pl, s, fa, par, hb + am));
+    a_axpy(-sg, y, q);
+  }
+  if (!cs.in || !((pl.dirs >> a) & 1)) return;
+  a_axpy(w1, transport(lds_m3(sh[a][0], lane), q), f);
+  double2* out = F + (int64_t(par) * 4 + a) * 9 * g.Vh + h;
+  double2 v[9];
+  v[0] = make_double2(0.0, f.d.x);
+  v[4] = make_double2(0.0, f.d.y);
+  v[8] = make_double2(0.0, -(f.d.x + f.d.y));
+  v[1] = f.o01;
+  v[2] = f.o02;
+  v[5] = f.o12;
+  v[3] = make_double2(-f.o01.x, f.o01.y);
+  v[6] = make_double2(-f.o02.x, f.o02.y);
+  v[7] = make_double2(-f.o12.x, f.o12.y);
+  const bool add = (pl.add >> a) & 1;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) {
+    if (add) {
+      const double2 o = out[int64_t(e) * g.Vh];
+      v[e].x += o.x;
+      v[e].y += o.y;
+    }
+    out[int64_t(e) * g.Vh] = v[e];
+  }
+}
+
+// The passes over planes [lo, hi) of the list 01, 02, 03, 12, 13, 23.
+Planes plane_pass(int lo, int hi, int accumulate, int* seen) {
+  Planes p{};
+  for (auto& r : p.slot)
+    for (int& v : r) v = -1;
+  int used = 0, i = 0;
+  for (int a = 0; a < 4; ++a)
+    for (int b = a + 1; b < 4; ++b, ++i) {
+      if (i < lo || i >= hi) continue;
+      p.slot[a][b] = p.slot[b][a] = p.n;
+      p.a[p.n] = a;
+      p.b[p.n] = b;
+      ++p.n;
+      used |= (1 << a) | (1 << b);
+    }
+  p.dirs = used;
+  p.add = accumulate ? 15 : *seen;
+  *seen |= used;
+  return p;
+}
+
+}  // namespace
+
+}  // namespace lqcd
+
+using namespace lqcd;
+
+extern "C" {
+
+size_t lqcd_gauge_force_staples_workspace_bytes(const lqcd_geom* g) {
+  if (check_geom(g)) return 0;
+  const KGeom k = make_kgeom(g);
+  return size_t(4) * 2 * 9 * size_t(k.Vh) * sizeof(double2);
+}
+
+int lqcd_gauge_force_staples(const lqcd_geom* g, const void* U64, double beta, double c1,
+                             int32_t accumulate, void* F, void* ws, size_t ws_bytes,
+                             void* stream) {
+  clear_error();
+  int rc;
+  if ((rc = check_geom(g)) || (rc = check_ptr(U64, "U64")) || (rc = check_ptr(F, "F")) ||
+      (rc = check_ptr(ws, "ws")))
+    return rc;
+  if (!std::isfinite(beta) || !std::isfinite(c1)) {
+    set_error("beta and c1 must be finite");
+    return LQCD_ERR_INVALID_ARG;
+  }
+  if (accumulate != 0 && accumulate != 1) {
+    set_error("accumulate must be 0 or 1");
+    return LQCD_ERR_INVALID_ARG;
+  }
+  if (F == U64 || ws == U64 || ws == F) {
+    set_error("F, U64 and ws must be distinct buffers");
+    return LQCD_ERR_INVALID_ARG;
+  }
+  const size_t need = lqcd_gauge_force_staples_workspace_bytes(g);
+  if (ws_bytes < need) {
+    set_error("gauge force workspace of %zu bytes is too small: %zu needed", ws_bytes, need);
+    return LQCD_ERR_WORKSPACE;
+  }
+  const KGeom k = make_kgeom(g);
+  const hipStream_t s = (hipStream_t)stream;
+  const double2* U = static_cast<const double2*>(U64);
+  double2* P = static_cast<double2*>(ws);
+  double2* out = static_cast<double2*>(F);
+  if (c1 == 0.0) return gauge_force_direct(k, U, beta, 0.0, accumulate, out, s);
+  // The required workspace holds the loop fields of three planes (two pass
+  // pairs, the second adding to F); given room for all six, one pair writes F.
+  const int step = ws_bytes >= 6 * kPlaneBytes * size_t(k.Vh) ? 6 : 3;
+  const int ty = chunk_tile(k.Ly, 16), tz = chunk_tile(k.Lz, 7);
+  const double w0 = -beta / 3.0 * (1.0 - 8.0 * c1), w1 = -beta / 3.0 * c1;
+  int seen = 0;
+  for (int lo = 0; lo < 6; lo += step) {
+    Planes p = plane_pass(lo, lo + step, accumulate, &seen);
+    p.sh = chunk_shift(k.Vh);
+    hipLaunchKernelGGL(k_loops, dim3(chunk_blocks(k.Vh)), dim3(64 * p.n), 0, s, k, U, p, w0, w1,
+                       ty, tz, P);
+    LQCD_LAUNCH_CHECK();
+    hipLaunchKernelGGL(k_loop_force, dim3(chunk_blocks(k.Vh)), dim3(256), 0, s, k, U, P, p, w1,
+                       ty, tz, out);
+    LQCD_LAUNCH_CHECK();
+  }
+  return LQCD_OK;
+}
+
+}  // extern "C"
