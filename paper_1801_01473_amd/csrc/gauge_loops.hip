@@ -41,55 +41,14 @@ namespace lqcd {
 
 namespace {
 
-// Traceless anti-Hermitian 3x3 matrix: entries 01, 02, 12 and the imaginary
-// parts of 00 and 11.  Stored as four complex planes.
-struct Alg {
-  double2 o01, o02, o12, d;
-};
-
-__device__ __forceinline__ Alg a_zero() {
-  const double2 z = make_double2(0.0, 0.0);
-  return Alg{z, z, z, z};
-}
-
-__device__ __forceinline__ void a_axpy(double w, const Alg& a, Alg& s) {
-  s.o01 = make_double2(fma(w, a.o01.x, s.o01.x), fma(w, a.o01.y, s.o01.y));
-  s.o02 = make_double2(fma(w, a.o02.x, s.o02.x), fma(w, a.o02.y, s.o02.y));
-  s.o12 = make_double2(fma(w, a.o12.x, s.o12.x), fma(w, a.o12.y, s.o12.y));
-  s.d = make_double2(fma(w, a.d.x, s.d.x), fma(w, a.d.y, s.d.y));
-}
-
-__device__ __forceinline__ double2 anti(const double2 a, const double2 b) {
-  return make_double2(0.5 * (a.x - b.x), 0.5 * (a.y + b.y));
-}
-
 // TA(a b^dag)
 __device__ __forceinline__ Alg ta_mul_dag(const M3& a, const M3& b) {
-  const M3 w = m_mul_dag(a, b);
-  const double tr = (w.e[0].y + w.e[4].y + w.e[8].y) / 3.0;
-  return Alg{anti(w.e[1], w.e[3]), anti(w.e[2], w.e[6]), anti(w.e[5], w.e[7]),
-             make_double2(w.e[0].y - tr, w.e[4].y - tr)};
+  return ta(m_mul_dag(a, b), 1.0);
 }
 
 // U^dag A U
 __device__ __forceinline__ Alg transport(const M3& u, const Alg& a) {
-  const double d2 = -(a.d.x + a.d.y);
-  M3 t;  // A U; row 1 and 2 of A hold -conj of the stored entries
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    double2 s = make_double2(-a.d.x * u.e[j].y, a.d.x * u.e[j].x);
-    cfma<double>(s, a.o01, u.e[3 + j]);
-    cfma<double>(s, a.o02, u.e[6 + j]);
-    t.e[j] = s;
-    s = make_double2(-a.d.y * u.e[3 + j].y, a.d.y * u.e[3 + j].x);
-    cfmac<double>(s, make_double2(-a.o01.x, -a.o01.y), u.e[j]);
-    cfma<double>(s, a.o12, u.e[6 + j]);
-    t.e[3 + j] = s;
-    s = make_double2(-d2 * u.e[6 + j].y, d2 * u.e[6 + j].x);
-    cfmac<double>(s, make_double2(-a.o02.x, -a.o02.y), u.e[j]);
-    cfmac<double>(s, make_double2(-a.o12.x, -a.o12.y), u.e[3 + j]);
-    t.e[6 + j] = s;
-  }
+  const M3 t = a_mul(a, u);
   auto entry = [&](int i, int j) {
     double2 s = cmulc<double>(u.e[i], t.e[j]);
     cfmac<double>(s, u.e[3 + i], t.e[3 + j]);
@@ -150,28 +109,6 @@ __device__ __forceinline__ void st_alg(double2* __restrict__ P, const Planes& pl
   p[n] = a.o02;
   p[2 * n] = a.o12;
   p[3 * n] = a.d;
-}
-
-__device__ __forceinline__ M3 lds_m3(const double2 (&s)[9][64], int lane) {
-  M3 m;
-#pragma unroll
-  for (int e = 0; e < 9; ++e) m.e[e] = s[e][lane];
-  return m;
-}
-
-// a b, with a read from LDS as it is used (no registers held for it)
-__device__ __forceinline__ M3 lds_mul(const double2 (&a)[9][64], int lane, const M3& b) {
-  M3 r;
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      double2 s = cmul<double>(a[3 * i][lane], b.e[j]);
-      cfma<double>(s, a[3 * i + 1][lane], b.e[3 + j]);
-      cfma<double>(s, a[3 * i + 2][lane], b.e[6 + j]);
-      r.e[3 * i + j] = s;
-    }
-  return r;
 }
 
 // One workgroup per 64 half indices of one parity, wave = plane.  The links
@@ -275,25 +212,17 @@ __global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* _
   if (!cs.in || !((pl.dirs >> a) & 1)) return;
   a_axpy(w1, transport(lds_m3(sh[a][0], lane), q), f);
   double2* out = F + (int64_t(par) * 4 + a) * 9 * g.Vh + h;
-  double2 v[9];
-  v[0] = make_double2(0.0, f.d.x);
-  v[4] = make_double2(0.0, f.d.y);
-  v[8] = make_double2(0.0, -(f.d.x + f.d.y));
-  v[1] = f.o01;
-  v[2] = f.o02;
-  v[5] = f.o12;
-  v[3] = make_double2(-f.o01.x, f.o01.y);
-  v[6] = make_double2(-f.o02.x, f.o02.y);
-  v[7] = make_double2(-f.o12.x, f.o12.y);
+  const M3 v = a_full(f);
   const bool add = (pl.add >> a) & 1;
 #pragma unroll
   for (int e = 0; e < 9; ++e) {
+    double2 z = v.e[e];
     if (add) {
       const double2 o = out[int64_t(e) * g.Vh];
-      v[e].x += o.x;
-      v[e].y += o.y;
+      z.x += o.x;
+      z.y += o.y;
     }
-    out[int64_t(e) * g.Vh] = v[e];
+    out[int64_t(e) * g.Vh] = z;
   }
 }
 

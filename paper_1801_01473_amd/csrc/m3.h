@@ -165,6 +165,117 @@ __device__ __forceinline__ M3 ld_m3(__amdgpu_buffer_rsrc_t r, int h, int Vh) {
   return m;
 }
 
+// Traceless anti-Hermitian 3x3 matrix: entries 01, 02, 12 and the imaginary
+// parts of 00 and 11.  Stored as four complex planes.
+struct Alg {
+  double2 o01, o02, o12, d;
+};
+
+__device__ __forceinline__ Alg a_zero() {
+  const double2 z = make_double2(0.0, 0.0);
+  return Alg{z, z, z, z};
+}
+
+__device__ __forceinline__ void a_axpy(double w, const Alg& a, Alg& s) {
+  s.o01 = make_double2(fma(w, a.o01.x, s.o01.x), fma(w, a.o01.y, s.o01.y));
+  s.o02 = make_double2(fma(w, a.o02.x, s.o02.x), fma(w, a.o02.y, s.o02.y));
+  s.o12 = make_double2(fma(w, a.o12.x, s.o12.x), fma(w, a.o12.y, s.o12.y));
+  s.d = make_double2(fma(w, a.d.x, s.d.x), fma(w, a.d.y, s.d.y));
+}
+
+__device__ __forceinline__ double2 neg(double2 a) { return make_double2(-a.x, -a.y); }
+
+// A u (the entries below the diagonal are minus the conjugates)
+__device__ __forceinline__ M3 a_mul(const Alg& a, const M3& u) {
+  const double d2 = -(a.d.x + a.d.y);
+  M3 t;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    double2 s = make_double2(-a.d.x * u.e[j].y, a.d.x * u.e[j].x);
+    cfma<double>(s, a.o01, u.e[3 + j]);
+    cfma<double>(s, a.o02, u.e[6 + j]);
+    t.e[j] = s;
+    s = make_double2(-a.d.y * u.e[3 + j].y, a.d.y * u.e[3 + j].x);
+    cfmac<double>(s, neg(a.o01), u.e[j]);
+    cfma<double>(s, a.o12, u.e[6 + j]);
+    t.e[3 + j] = s;
+    s = make_double2(-d2 * u.e[6 + j].y, d2 * u.e[6 + j].x);
+    cfmac<double>(s, neg(a.o02), u.e[j]);
+    cfmac<double>(s, neg(a.o12), u.e[3 + j]);
+    t.e[6 + j] = s;
+  }
+  return t;
+}
+
+// u A
+__device__ __forceinline__ M3 m_mul_a(const M3& u, const Alg& a) {
+  const double d2 = -(a.d.x + a.d.y);
+  M3 t;
+#pragma unroll
+  for (int i = 0; i < 9; i += 3) {
+    double2 s = make_double2(-a.d.x * u.e[i].y, a.d.x * u.e[i].x);
+    cfmac<double>(s, neg(a.o01), u.e[i + 1]);
+    cfmac<double>(s, neg(a.o02), u.e[i + 2]);
+    t.e[i] = s;
+    s = make_double2(-a.d.y * u.e[i + 1].y, a.d.y * u.e[i + 1].x);
+    cfma<double>(s, a.o01, u.e[i]);
+    cfmac<double>(s, neg(a.o12), u.e[i + 2]);
+    t.e[i + 1] = s;
+    s = make_double2(-d2 * u.e[i + 2].y, d2 * u.e[i + 2].x);
+    cfma<double>(s, a.o02, u.e[i]);
+    cfma<double>(s, a.o12, u.e[i + 1]);
+    t.e[i + 2] = s;
+  }
+  return t;
+}
+
+// s TA(w)
+__device__ __forceinline__ Alg ta(const M3& w, double s) {
+  const double tr = (w.e[0].y + w.e[4].y + w.e[8].y) / 3.0, h = 0.5 * s;
+  return Alg{make_double2(h * (w.e[1].x - w.e[3].x), h * (w.e[1].y + w.e[3].y)),
+             make_double2(h * (w.e[2].x - w.e[6].x), h * (w.e[2].y + w.e[6].y)),
+             make_double2(h * (w.e[5].x - w.e[7].x), h * (w.e[5].y + w.e[7].y)),
+             make_double2(s * (w.e[0].y - tr), s * (w.e[4].y - tr))};
+}
+
+// the full matrix
+__device__ __forceinline__ M3 a_full(const Alg& a) {
+  M3 r;
+  r.e[0] = make_double2(0.0, a.d.x);
+  r.e[4] = make_double2(0.0, a.d.y);
+  r.e[8] = make_double2(0.0, -(a.d.x + a.d.y));
+  r.e[1] = a.o01;
+  r.e[2] = a.o02;
+  r.e[5] = a.o12;
+  r.e[3] = make_double2(-a.o01.x, a.o01.y);
+  r.e[6] = make_double2(-a.o02.x, a.o02.y);
+  r.e[7] = make_double2(-a.o12.x, a.o12.y);
+  return r;
+}
+
+// A matrix of the wave's 64 lanes in LDS, one element after the other.
+__device__ __forceinline__ M3 lds_m3(const double2 (&s)[9][64], int lane) {
+  M3 m;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) m.e[e] = s[e][lane];
+  return m;
+}
+
+// a b, with a read from LDS as it is used (no registers held for it)
+__device__ __forceinline__ M3 lds_mul(const double2 (&a)[9][64], int lane, const M3& b) {
+  M3 r;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      double2 s = cmul<double>(a[3 * i][lane], b.e[j]);
+      cfma<double>(s, a[3 * i + 1][lane], b.e[3 + j]);
+      cfma<double>(s, a[3 * i + 2][lane], b.e[6 + j]);
+      r.e[3 * i + j] = s;
+    }
+  return r;
+}
+
 }  // namespace
 
 }  // namespace lqcd
