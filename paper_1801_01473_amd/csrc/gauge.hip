@@ -29,6 +29,7 @@ namespace {
 
 constexpr int kGaugeBlock = 128;
 constexpr int kMdBlock = 256;
+constexpr int kReduceBlock = 1024;
 
 // Weighted staple sum of the link U_mu(x): Tr[U_mu(x) A] runs over every
 // plaquette (weight c0) and every 1x2 rectangle (weight c1) through the link,
@@ -157,49 +158,9 @@ __global__ void __launch_bounds__(kGaugeBlock) k_gauge_force(KGeom g, const doub
   }
 }
 
-// Sum over the loops whose first corner is the thread's site of
-// w (1 - Re Tr W / 3): plaquettes mu < nu, 2 x 1 rectangles for every mu != nu.
-__global__ void __launch_bounds__(kGaugeBlock) k_gauge_action(KGeom g, const double2* __restrict__ U,
-                                                              double c0, double c1,
-                                                              double* __restrict__ part) {
-  __shared__ double lds[kGaugeBlock / 64];
-  const int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  double s = 0.0;
-  if (idx < int64_t(2) * g.Vh) {
-    const int par = int(idx / g.Vh), h = int(idx % g.Vh);
-    const C4 x = site_c4(g, h, par);
-#pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {
-      const C4 xp = shift(g, x, mu, 1);
-#pragma unroll 1
-      for (int nu = 0; nu < 4; ++nu) {
-        if (nu == mu) continue;
-        const C4 xn = shift(g, x, nu, 1);
-        if (mu < nu) {  // U_mu(x) U_nu(x+mu) U_mu(x+nu)^dag U_nu(x)^dag
-          M3 t = m_mul(link(g, U, x, mu), link(g, U, xp, nu));
-          t = m_mul_dag(t, link(g, U, xn, mu));
-          t = m_mul_dag(t, link(g, U, x, nu));
-          s += c0 * (1.0 - re_tr(t) / 3.0);
-        }
-        if (c1 != 0.0) {
-          // U_mu(x) U_mu(x+mu) U_nu(x+2mu) U_mu(x+mu+nu)^dag U_mu(x+nu)^dag U_nu(x)^dag
-          M3 t = m_mul(link(g, U, x, mu), link(g, U, xp, mu));
-          t = m_mul(t, link(g, U, shift(g, xp, mu, 1), nu));
-          t = m_mul_dag(t, link(g, U, shift(g, xp, nu, 1), mu));
-          t = m_mul_dag(t, link(g, U, xn, mu));
-          t = m_mul_dag(t, link(g, U, x, nu));
-          s += c1 * (1.0 - re_tr(t) / 3.0);
-        }
-      }
-    }
-  }
-  s = block_sum(s, lds);
-  if (threadIdx.x == 0) part[blockIdx.x] = s;
-}
-
-__global__ void __launch_bounds__(kMdBlock) k_reduce_one(const double* __restrict__ part, int n,
+__global__ void __launch_bounds__(kReduceBlock) k_reduce_one(const double* __restrict__ part, int n,
                                                           double scale, double* __restrict__ out) {
-  __shared__ double lds[kMdBlock / 64];
+  __shared__ double lds[kReduceBlock / 64];
   double s = strided_sum(part, n);
   s = block_sum(s, lds);
   if (threadIdx.x == 0) *out = scale * s;
@@ -360,7 +321,7 @@ int check_c1(double beta, double c1) {
 
 int reduce_to_host(const double* part, int nb, double scale, double* out_dev, double* host,
                    hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_one, dim3(1), dim3(kMdBlock), 0, s, part, nb, scale, out_dev);
+  hipLaunchKernelGGL(k_reduce_one, dim3(1), dim3(kReduceBlock), 0, s, part, nb, scale, out_dev);
   LQCD_LAUNCH_CHECK();
   LQCD_HIP_TRY(hipMemcpyAsync(host, out_dev, sizeof(double), hipMemcpyDeviceToHost, s));
   LQCD_HIP_TRY(hipStreamSynchronize(s));
@@ -441,12 +402,10 @@ int lqcd_gauge_action(const lqcd_geom* g, const void* U64, double beta, double c
     return LQCD_ERR_WORKSPACE;
   }
   const KGeom k = make_kgeom(g);
-  const int nb = int((int64_t(2) * k.Vh + kGaugeBlock - 1) / kGaugeBlock);
+  const int nb = int(gauge_action_blocks(k));
   double* part = static_cast<double*>(ws);
   const hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(k_gauge_action, dim3(nb), dim3(kGaugeBlock), 0, s, k, (const double2*)U64,
-                     1.0 - 8.0 * c1, c1, part);
-  LQCD_LAUNCH_CHECK();
+  if ((rc = gauge_action_partials(k, (const double2*)U64, c1, part, s))) return rc;
   return reduce_to_host(part, nb, beta, part + nb + 16, S, s);
 }
 

@@ -111,57 +111,123 @@ __device__ __forceinline__ void st_alg(double2* __restrict__ P, const Planes& pl
   p[3 * n] = a.d;
 }
 
-// One workgroup per 64 half indices of one parity, wave = plane.  The links
-// U_mu(x) and U_mu(x + mu), which three planes use (twice each), go through LDS.
-__global__ void __launch_bounds__(384, 3) k_loops(KGeom g, const double2* __restrict__ U,
-                                               const Planes pl, double w0, double w1, int ty,
-                                               int tz, double2* __restrict__ P) {
-  __shared__ double2 sh[2][4][9][64];  // U_mu(x), U_mu(x + mu)
-  const ChunkSite cs = chunk_site(g, ty, tz);
-  const int h = cs.h, par = cs.par, opp = 1 - par, lane = cs.lane, task = cs.task;
+// What a wave of the plane kernels works with: one plane of 64 sites of one
+// parity, its links by displacement, and the links U_mu(x) and U_mu(x + mu) of
+// the workgroup's sites in LDS (three planes use each of them, twice each).
+using Ahead = double2[2][4][9][64];
+
+struct PlaneSite {
+  __amdgpu_buffer_rsrc_t a_s, b_s, a_o, b_o;  // links leaving sites of the same / other parity
+  int h, a1, b1, ab, a2, b2;                  // x, x + a, x + b, x + a + b, x + 2a, x + 2b
+};
+
+__device__ __forceinline__ PlaneSite plane_site(const KGeom& g, const double2* __restrict__ U,
+                                                const ChunkSite& cs, int n, int a, int b,
+                                                Ahead& sh) {
+  const int h = cs.h, par = cs.par, opp = 1 - par;
   const C4 x = site_c4(g, h, par);
-  for (int m = task; m < 8; m += pl.n) {
+  for (int m = cs.task; m < 8; m += n) {
     const int mu = m & 3, far = m >> 2;
     const M3 u = ld_m3(link_res(g, U, far ? opp : par, mu),
                        h + (far ? axis(g, x, mu).off(1) : 0), g.Vh);
 #pragma unroll
-    for (int e = 0; e < 9; ++e) sh[far][mu][e][lane] = u.e[e];
+    for (int e = 0; e < 9; ++e) sh[far][mu][e][cs.lane] = u.e[e];
   }
-  const int a = pl.a[task], b = pl.b[task];
   const Axis xa = axis(g, x, a), xb = axis(g, x, b);
-  const int a1 = h + xa.off(1), b1 = h + xb.off(1);
-  const int ab = a1 + (b1 - h), a2 = h + xa.off(2), b2 = h + xb.off(2);
-  // links leaving sites of the same and of the other parity
-  const auto a_s = link_res(g, U, par, a), b_s = link_res(g, U, par, b);
-  const auto a_o = link_res(g, U, opp, a), b_o = link_res(g, U, opp, b);
+  PlaneSite p;
+  p.h = h;
+  p.a1 = h + xa.off(1);
+  p.b1 = h + xb.off(1);
+  p.ab = p.a1 + (p.b1 - h);
+  p.a2 = h + xa.off(2);
+  p.b2 = h + xb.off(2);
+  p.a_s = link_res(g, U, par, a);
+  p.b_s = link_res(g, U, par, b);
+  p.a_o = link_res(g, U, opp, a);
+  p.b_o = link_res(g, U, opp, b);
   __syncthreads();
+  return p;
+}
+
+// One workgroup per 64 half indices of one parity, wave = plane.
+__global__ void __launch_bounds__(384, 3) k_loops(KGeom g, const double2* __restrict__ U,
+                                                  const Planes pl, double w0, double w1, int ty,
+                                                  int tz, double2* __restrict__ P) {
+  __shared__ Ahead sh;
+  const ChunkSite cs = chunk_site(g, ty, tz);
+  const int lane = cs.lane, task = cs.task, a = pl.a[task], b = pl.b[task];
+  const PlaneSite p = plane_site(g, U, cs, pl.n, a, b, sh);
   if (!cs.in) return;
   // (the barriers keep the compiler from loading every section's links at
   // once: 168 registers without spilling, so two workgroups share a CU)
-  const M3 c1 = lds_mul(sh[0][a], lane, ld_m3(b_o, a1, g.Vh));  // a, b
+  const M3 c1 = lds_mul(sh[0][a], lane, ld_m3(p.b_o, p.a1, g.Vh));  // a, b
   __builtin_amdgcn_sched_barrier(0);
-  const M3 c2 = lds_mul(sh[0][b], lane, ld_m3(a_o, b1, g.Vh));  // b, a
+  const M3 c2 = lds_mul(sh[0][b], lane, ld_m3(p.a_o, p.b1, g.Vh));  // b, a
   Alg sum = a_zero();
   a_axpy(w0, ta_mul_dag(c1, c2), sum);
   __builtin_amdgcn_sched_barrier(0);
   {
-    const M3 r = m_mul(c2, ld_m3(a_s, ab, g.Vh));  // b, a, a
-    const M3 e = lds_mul(sh[1][a], lane, ld_m3(b_s, a2, g.Vh));
-    const M3 l = lds_mul(sh[0][a], lane, e);    // a, a, b
+    const M3 r = m_mul(c2, ld_m3(p.a_s, p.ab, g.Vh));  // b, a, a
+    const M3 e = lds_mul(sh[1][a], lane, ld_m3(p.b_s, p.a2, g.Vh));
+    const M3 l = lds_mul(sh[0][a], lane, e);  // a, a, b
     const Alg ra = ta_mul_dag(l, r);
-    st_alg(P, pl, task, 1, par, h, ra);
+    st_alg(P, pl, task, 1, cs.par, p.h, ra);
     a_axpy(w1, ra, sum);
   }
   __builtin_amdgcn_sched_barrier(0);
   {
-    const M3 l = m_mul(c1, ld_m3(b_s, ab, g.Vh));  // a, b, b
-    const M3 e = lds_mul(sh[1][b], lane, ld_m3(a_s, b2, g.Vh));
-    const M3 r = lds_mul(sh[0][b], lane, e);    // b, b, a
+    const M3 l = m_mul(c1, ld_m3(p.b_s, p.ab, g.Vh));  // a, b, b
+    const M3 e = lds_mul(sh[1][b], lane, ld_m3(p.a_s, p.b2, g.Vh));
+    const M3 r = lds_mul(sh[0][b], lane, e);  // b, b, a
     const Alg rb = ta_mul_dag(l, r);
-    st_alg(P, pl, task, 2, par, h, rb);
+    st_alg(P, pl, task, 2, cs.par, p.h, rb);
     a_axpy(w1, rb, sum);
   }
-  st_alg(P, pl, task, 0, par, h, sum);
+  st_alg(P, pl, task, 0, cs.par, p.h, sum);
+}
+
+// Re Tr[a b^dag]
+__device__ __forceinline__ double re_tr_dag(const M3& a, const M3& b) {
+  double s = 0.0;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) s = fma(a.e[e].x, b.e[e].x, fma(a.e[e].y, b.e[e].y, s));
+  return s;
+}
+
+// The action of the loops whose first corner is x, one plane per wave as in
+// k_loops: w (1 - Re Tr / 3) of the plaquette and of both rectangles, 8 products
+// per plane (the last one of each loop is only a trace).  24^3 x 48: 0.38 ms, bound
+// by 44 link matrices per site from L2 (4.2 GB at 11 TB/s); one thread per site
+// over all loops, 13 products per plane, took 1.03 ms.
+__global__ void __launch_bounds__(384, 3) k_loop_action(KGeom g, const double2* __restrict__ U,
+                                                        const Planes pl, double c0, double c1,
+                                                        int ty, int tz,
+                                                        double* __restrict__ part) {
+  __shared__ Ahead sh;
+  __shared__ double lds[6];
+  const ChunkSite cs = chunk_site(g, ty, tz);
+  const int lane = cs.lane, a = pl.a[cs.task], b = pl.b[cs.task];
+  const PlaneSite p = plane_site(g, U, cs, pl.n, a, b, sh);
+  const M3 ca = lds_mul(sh[0][a], lane, ld_m3(p.b_o, p.a1, g.Vh));  // a, b
+  __builtin_amdgcn_sched_barrier(0);
+  const M3 cb = lds_mul(sh[0][b], lane, ld_m3(p.a_o, p.b1, g.Vh));  // b, a
+  double s = c0 * (1.0 - re_tr_dag(ca, cb) / 3.0);
+  if (c1 != 0.0) {
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const M3 r = m_mul(cb, ld_m3(p.a_s, p.ab, g.Vh));  // b, a, a
+      const M3 e = lds_mul(sh[1][a], lane, ld_m3(p.b_s, p.a2, g.Vh));
+      s += c1 * (1.0 - re_tr_dag(lds_mul(sh[0][a], lane, e), r) / 3.0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const M3 l = m_mul(ca, ld_m3(p.b_s, p.ab, g.Vh));  // a, b, b
+      const M3 e = lds_mul(sh[1][b], lane, ld_m3(p.a_s, p.b2, g.Vh));
+      s += c1 * (1.0 - re_tr_dag(l, lds_mul(sh[0][b], lane, e)) / 3.0);
+    }
+  }
+  s = block_sum(cs.in ? s : 0.0, lds);
+  if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
 // One workgroup per 64 half indices of one parity, wave = direction a.  The
@@ -248,6 +314,18 @@ Planes plane_pass(int lo, int hi, int accumulate, int* seen) {
 }
 
 }  // namespace
+
+unsigned gauge_action_blocks(const KGeom& k) { return chunk_blocks(k.Vh); }
+
+int gauge_action_partials(const KGeom& k, const double2* U, double c1, double* part,
+                          hipStream_t s) {
+  int seen = 0;
+  const Planes p = plane_pass(0, 6, 0, &seen);
+  hipLaunchKernelGGL(k_loop_action, dim3(gauge_action_blocks(k)), dim3(64 * p.n), 0, s, k, U, p,
+                     1.0 - 8.0 * c1, c1, chunk_tile(k.Ly, 16), chunk_tile(k.Lz, 7), part);
+  LQCD_LAUNCH_CHECK();
+  return LQCD_OK;
+}
 
 }  // namespace lqcd
 

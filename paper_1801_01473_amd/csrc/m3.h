@@ -77,8 +77,6 @@ __device__ __forceinline__ void m_axpy(double w, const M3& a, M3& acc) {
   }
 }
 
-__device__ __forceinline__ double re_tr(const M3& a) { return a.e[0].x + a.e[4].x + a.e[8].x; }
-
 // Coordinates with periodic wrap (named fields: a direction index chosen at
 // run time selects among them, so nothing is indexed dynamically), and the
 // link U_mu at a site.
