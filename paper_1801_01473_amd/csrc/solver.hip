@@ -1504,6 +1504,7 @@ int core_solve(const Ctx& c, Core& k, const double* m2s_host, const double* delt
   GlobalFlags f{};
   if ((rc = read_flags(c, &f))) return rc;
   debug_dump(c, k, "init");
+  bool low = mixed && !k.two_phase;  // FP32 partial sums exist
   if (k.two_phase) {
     // FP64 opening phase until every system's residual is below mixed_switch |b|
     if ((rc = run_phase(c, k, k.pre, false, true, &iters_run, &f))) return rc;
@@ -1520,13 +1521,16 @@ int core_solve(const Ctx& c, Core& k, const double* m2s_host, const double* delt
       LQCD_LAUNCH_CHECK();
       hipLaunchKernelGGL(k_sc_phase2, dim3(1), dim3(64), 0, s, st, k.nsys, k.nshift);
       LQCD_LAUNCH_CHECK();
+      low = true;
       debug_dump(c, k, "switch");
     }
   }
   if ((rc = run_phase(c, k, k.main, mixed, false, &iters_run, &f))) return rc;
-  // a mixed solve that stopped on the iteration limit still folds its FP32 sums in
+  // a mixed solve that stopped on the iteration limit still folds its FP32 sums
+  // in; one that the FP64 opening phase finished has none (its solutions are
+  // complete, and the FP32 vectors were never written)
   if (mixed && !f.error) {
-    if ((rc = launch_reliable(c, k, s))) return rc;
+    if (low && (rc = launch_reliable(c, k, s))) return rc;
   } else if (k.win > 1 && (rc = launch_flush(c, k, k.main, s))) {
     return rc;
   }
