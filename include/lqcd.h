@@ -152,8 +152,8 @@ int lqcd_unpack_spinor(const lqcd_geom *g, int parity, int prec, const void *pac
  * precision, format, nrhs, mode) and cached for the process; that first call
  * allocates temporary scratch and synchronises the stream.  Environment:
  * LQCD_TUNE=0 uses a fixed default instead, LQCD_TUNE_VERBOSE=1 prints the
- * timings, LQCD_DSLASH_CFG="block,rhs_block,xcd,tz[,nt,occ,ilv,lf,hh,ty,ns]"
- * pins one configuration (testing and profiling), LQCD_TUNE_CACHE=<file>
+ * timings, LQCD_DSLASH_CFG="block,rhs_block,xcd,tz[,nt,occ,ilv,lf,hh,ty,ns,tm,tp,
+ * mf,sp]" pins one configuration (testing and profiling), LQCD_TUNE_CACHE=<file>
  * keeps tuned configurations across processes (one text line per shape,
  * keyed by GPU architecture and CU count; entries that are not valid for the
  * shape are ignored).
@@ -277,6 +277,9 @@ int lqcd_cg(const lqcd_geom *g, const lqcd_solver_params *p, const void *U64_pac
  * the same stencil launch configurations the results are the same bits as
  * with separate rows, which the environment variable LQCD_RHS_PAIRS=0 selects
  * (comparisons).  b, x and the workspace size are unaffected.
+ * On small lattices the iteration's scalars are computed inside the stencil and
+ * the update, with the same bits as in kernels of their own, which
+ * LQCD_FUSED_SCALARS=0 selects (comparisons).
  * 1 <= nrhs <= 64.
  */
 int lqcd_cg_multishift(const lqcd_geom *g, const lqcd_solver_params *p,

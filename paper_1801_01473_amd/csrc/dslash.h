@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "solver.h"
 
 namespace lqcd {
 
@@ -60,6 +61,17 @@ struct DslashCall {
   // right-hand sides with one 16-byte access (same arithmetic, same bits).
   int pairs = 0;
   double* partials = nullptr; // [nrhs][nblocks]
+  // Step length inside the fused CG update (k_dslash_split only): when sys is
+  // set, every workgroup sums the partials of |D_oe p|^2 (step_t, step_nt of
+  // them per right-hand side) and |p|^2 (step_p, step_np), forms alpha = a of
+  // its systems from them, and the first site block stores the state.
+  SysState* sys = nullptr;
+  GlobalFlags* flags = nullptr;
+  int nshift = 0;
+  const double* step_t = nullptr;
+  int step_nt = 0;
+  const double* step_p = nullptr;
+  int step_np = 0;
 };
 
 struct DslashCfg {
@@ -87,6 +99,8 @@ struct DslashCfg {
   int tp = 2;       // t-march: lanes per column sharing its eight right-hand sides (2 or 4)
   int mf = 0;       // 1: the matrix-core contraction (k_dslash_mfma; FP32, 12-real, plain
                     // mode, rhs_block 8, tm = 0); pinned only, never picked by the tuner
+  int sp = 0;       // 1: the four directions of a site on four waves (k_dslash_split; block 256,
+                    // rhs_block 1 or 2, the plain schedule without tiles)
 };
 
 // Dynamic LDS a workgroup reserves so that at most occ waves per SIMD are resident.
@@ -107,6 +121,7 @@ inline int dslash_tm_column_blocks(const KGeom& g, const DslashCfg& c) {
 // Number of workgroups along the site dimension for a configuration.
 inline int dslash_nblocks(const KGeom& g, const DslashCfg& c) {
   if (c.tm > 0) return dslash_tm_column_blocks(g, c) * (g.Lt / c.tm);
+  if (c.sp == 1) return (g.Vh + 63) / 64;
   return (g.Vh + c.block - 1) / c.block;
 }
 // Largest partials array any configuration can need.
@@ -122,6 +137,10 @@ int dslash_launch(const DslashCall& c, const DslashCfg& cfg, hipStream_t st);
 template <typename R, int NE>
 int dslash_launch_fmt(const DslashCall& c, const DslashCfg& cfg, hipStream_t st);
 int dslash_launch_res(const DslashCall& c, const DslashCfg& cfg, hipStream_t st);
+
+// The direction-split kernels (dslash_split.hip).
+bool dslash_split_supported(const DslashCall& c, const DslashCfg& cfg);
+int dslash_split_launch(const DslashCall& c, const DslashCfg& cfg, hipStream_t st);
 
 // The t-march kernel family (dslash_tm.hip).
 bool dslash_tm_supported(const DslashCall& c, const DslashCfg& cfg);

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "dslash.h"
+#include "sysred.h"
 
 namespace lqcd {
 
@@ -35,7 +36,12 @@ int dslash_launch(const DslashCall& c, const DslashCfg& cfg, hipStream_t st) {
       return LQCD_ERR_UNSUPPORTED;
     }
   }
+  if (c.sys && (cfg.sp != 1 || c.mode != DM_CG)) {
+    set_error("the step length inside the stencil needs the direction-split CG update");
+    return LQCD_ERR_UNSUPPORTED;
+  }
   if (cfg.tm > 0) return dslash_tm_launch(c, cfg, st);
+  if (cfg.sp == 1) return dslash_split_launch(c, cfg, st);
   if (cfg.mf == 1) return dslash_mfma_launch(c, cfg, st);
   if (cfg.tz < 0 || (cfg.tz > 0 && c.g.Lz % cfg.tz != 0) || cfg.ty < 0 ||
       (cfg.ty > 0 && c.g.Ly % cfg.ty != 0)) {
@@ -92,12 +98,21 @@ bool tuning_verbose() {
 
 // ---- optional on-disk tuning cache (LQCD_TUNE_CACHE=file) ----------------
 // One line per tuned shape:
-// "<key>;<block>,<B>,<xcd>,<tz>,<nt>,<occ>,<ilv>,<lf>,<hh>,<ty>[,<ns>[,<tm>,<tp>]]"
+// "<key>;<block>,<B>,<xcd>,<tz>,<nt>,<occ>,<ilv>,<lf>,<hh>,<ty>[,<ns>[,<tm>,<tp>[,<sp>]]]"
 // where the key names the cache format, the GPU architecture and CU count,
 // the geometry, precision, link format, RHS count, forced RHS block and
 // mode.  Lines that do not parse, or whose configuration is not valid for
 // the shape, are ignored (that shape is tuned again).
 constexpr int kTuneCacheFormat = 1;
+
+// Half volumes up to which the direction-split stencil is a candidate.
+constexpr int kSplitMaxVh = 1 << 18;
+
+// What the split kernel saves elsewhere when it can take over the step length
+// (up to kFusedPartials partials): the one-workgroup kernels of the scalars, 5
+// and 4 us a launch at 16^4, against about 1 us more in the CG kernels each.
+// Its times in CG mode are ranked with this credit.
+constexpr float kFusedCreditMs = 0.006f;
 
 const char* tune_cache_path() {
   const char* e = std::getenv("LQCD_TUNE_CACHE");
@@ -132,6 +147,7 @@ bool cfg_valid(const DslashCall& c, const DslashCfg& f, int forced) {
          (f.ilv == 0 || f.ilv == 1) && f.occ >= 0 && dslash_lds_bytes(f) >= 0 &&
          dslash_lds_bytes(f) <= 64 * 1024 && f.tm >= 0 &&
          (f.tm == 0 || dslash_tm_supported(c, f)) &&
+         (f.sp == 0 || (f.sp == 1 && dslash_split_supported(c, f))) &&
          (!c.pairs || (f.rhs_block % 2 == 0 && f.tm == 0 && f.mf == 0));
 }
 
@@ -148,10 +164,10 @@ bool tune_cache_lookup(const char* path, const std::string& key, const DslashCal
     *semi = '\0';
     if (key != line) continue;
     DslashCfg v;
-    const int n = std::sscanf(semi + 1, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &v.block,
+    const int n = std::sscanf(semi + 1, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &v.block,
                               &v.rhs_block, &v.xcd, &v.tz, &v.nt, &v.occ, &v.ilv, &v.lf, &v.hh,
-                              &v.ty, &v.ns, &v.tm, &v.tp);
-    if (n != 10 && n != 11 && n != 13) continue;
+                              &v.ty, &v.ns, &v.tm, &v.tp, &v.sp);
+    if (n != 10 && n != 11 && n != 13 && n != 14) continue;
     if (!cfg_valid(c, v, forced)) continue;
     *out = v;
     found = true;
@@ -163,8 +179,9 @@ bool tune_cache_lookup(const char* path, const std::string& key, const DslashCal
 void tune_cache_store(const char* path, const std::string& key, const DslashCfg& v) {
   FILE* f = std::fopen(path, "a");
   if (!f) return;  // the cache is an optimisation; an unwritable file only costs tuning
-  std::fprintf(f, "%s;%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d\n", key.c_str(), v.block,
-               v.rhs_block, v.xcd, v.tz, v.nt, v.occ, v.ilv, v.lf, v.hh, v.ty, v.ns, v.tm, v.tp);
+  std::fprintf(f, "%s;%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d\n", key.c_str(), v.block,
+               v.rhs_block, v.xcd, v.tz, v.nt, v.occ, v.ilv, v.lf, v.hh, v.ty, v.ns, v.tm, v.tp,
+               v.sp);
   std::fclose(f);
 }
 
@@ -184,16 +201,16 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     set_error("right-hand-side pairs need an RHS block of 2, 4 or 8");
     return LQCD_ERR_INVALID_ARG;
   }
-  // LQCD_DSLASH_CFG="block,rhs_block,xcd,tz[,nt,occ,ilv,lf,hh,ty,ns,tm,tp,mf]" pins the
+  // LQCD_DSLASH_CFG="block,rhs_block,xcd,tz[,nt,occ,ilv,lf,hh,ty,ns,tm,tp,mf,sp]" pins the
   // configuration (testing, profiling).  A t-march or matrix-core configuration
   // applies only where that kernel exists (t-march: 8 right-hand sides or more,
   // 12-real links, the plain and fused modes; matrix cores: FP32, 12-real, plain
   // mode without norms); other calls fall back to its k_dslash settings.
   if (const char* e = std::getenv("LQCD_DSLASH_CFG")) {
     DslashCfg f;
-    if (std::sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &f.block, &f.rhs_block,
+    if (std::sscanf(e, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &f.block, &f.rhs_block,
                     &f.xcd, &f.tz, &f.nt, &f.occ, &f.ilv, &f.lf, &f.hh, &f.ty, &f.ns, &f.tm,
-                    &f.tp, &f.mf) >= 4) {
+                    &f.tp, &f.mf, &f.sp) >= 4) {
       if (forced) f.rhs_block = forced;
       if (c.pairs && f.rhs_block == 1) f.rhs_block = 2;  // pairs load two rows at once
       if (f.tm > 0 && (c.nrhs < 8 || !dslash_tm_supported(c, f))) {
@@ -201,6 +218,7 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
         if (f.rhs_block > c.nrhs) f.rhs_block = 1;
       }
       if (f.mf == 1 && !dslash_mfma_supported(c, f)) f.mf = 0;
+      if (f.sp == 1 && !dslash_split_supported(c, f)) f.sp = 0;
       *out = f;
       return LQCD_OK;
     }
@@ -257,6 +275,21 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
             cand.push_back(v);
           }
         }
+    }
+
+  // the direction-split kernel, where one thread per site leaves the chip idle
+  if (c.g.Vh <= kSplitMaxVh)
+    for (int b : {1, 2}) {
+      if (forced ? b != forced : b > c.nrhs) continue;
+      if (c.pairs && b == 1) continue;
+      for (int x : {0, 1}) {
+        DslashCfg v;
+        v.block = 256;
+        v.rhs_block = b;
+        v.xcd = x;
+        v.sp = 1;
+        cand.push_back(v);
+      }
     }
 
   const size_t vec = size_t(3) * c.g.Vh * 2 * (c.prec == LQCD_F32 ? 4 : 8);
@@ -325,13 +358,19 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     return LQCD_OK;
   };
 
+  const bool fusable = cg && (c.g.Vh + 63) / 64 <= kFusedPartials;
+  auto ranked = [&](float ms, const DslashCfg& cfg) {
+    return fusable && cfg.sp == 1 ? ms - kFusedCreditMs : ms;
+  };
   float best_ms = 1e30f;
   int rc = LQCD_OK;
   std::vector<std::pair<float, DslashCfg>> timed;
   const size_t stage1 = cand.size();
   size_t stage2 = size_t(-1);
   auto top3 = [&]() {
-    std::vector<std::pair<float, DslashCfg>> s1 = timed;
+    std::vector<std::pair<float, DslashCfg>> s1;
+    for (const auto& tk : timed)
+      if (tk.second.sp == 0) s1.push_back(tk);  // the split kernel has no schedules
     std::sort(s1.begin(), s1.end(),
               [](const std::pair<float, DslashCfg>& a, const std::pair<float, DslashCfg>& b) {
                 return a.first < b.first;
@@ -349,14 +388,15 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
       rc = LQCD_ERR_HIP;
       break;
     }
+    ms = ranked(ms, cfg);
     if (runs) timed.push_back({ms, cfg});
     if (runs && tuning_verbose())
       fprintf(stderr,
               "[lqcd tune] L=%dx%dx%dx%d prec=%d fmt=%d nrhs=%d mode=%d block=%d B=%d xcd=%d "
-              "ty=%d tz=%d nt=%d occ=%d ilv=%d lf=%d hh=%d ns=%d tm=%d tp=%d: %.2f us\n",
+              "ty=%d tz=%d nt=%d occ=%d ilv=%d lf=%d hh=%d ns=%d tm=%d tp=%d sp=%d: %.2f us\n",
               c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, t.prec, t.fmt, c.nrhs, t.mode, cfg.block,
               cfg.rhs_block, cfg.xcd, cfg.ty, cfg.tz, cfg.nt, cfg.occ, cfg.ilv, cfg.lf, cfg.hh,
-              cfg.ns, cfg.tm, cfg.tp, 1000.0 * ms);
+              cfg.ns, cfg.tm, cfg.tp, cfg.sp, 1000.0 * ms);
     if (runs && ms < best_ms) {
       best_ms = ms;
       best = cfg;
@@ -370,7 +410,8 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
           seeds[1].second.xcd == seeds[2].second.xcd) {
         const std::pair<float, DslashCfg>* other = nullptr;
         for (const auto& tk : timed)
-          if (tk.second.xcd != seeds[0].second.xcd && (!other || tk.first < other->first))
+          if (tk.second.sp == 0 && tk.second.xcd != seeds[0].second.xcd &&
+              (!other || tk.first < other->first))
             other = &tk;
         if (other) seeds[2] = *other;
       }
@@ -449,7 +490,7 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
           rc = LQCD_ERR_HIP;
           break;
         }
-        rt[k].push_back(ms);
+        rt[k].push_back(ranked(ms, timed[k].second));
       }
     if (rc == LQCD_OK) {
       float best_med = 1e30f;
@@ -475,10 +516,10 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
   if (tuning_verbose())
     fprintf(stderr,
             "[lqcd tune] chosen L=%dx%dx%dx%d prec=%d fmt=%d nrhs=%d mode=%d: block=%d B=%d "
-            "xcd=%d ty=%d tz=%d nt=%d occ=%d ilv=%d lf=%d hh=%d ns=%d tm=%d tp=%d (%.2f us)\n",
+            "xcd=%d ty=%d tz=%d nt=%d occ=%d ilv=%d lf=%d hh=%d ns=%d tm=%d tp=%d sp=%d (%.2f us)\n",
             c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, t.prec, t.fmt, c.nrhs, t.mode, best.block,
             best.rhs_block, best.xcd, best.ty, best.tz, best.nt, best.occ, best.ilv, best.lf,
-            best.hh, best.ns, best.tm, best.tp, 1000.0 * best_ms);
+            best.hh, best.ns, best.tm, best.tp, best.sp, 1000.0 * best_ms);
   *out = best;
   return LQCD_OK;
 }

@@ -33,6 +33,9 @@ struct alignas(16) SysState {
   double m2s;      // base diagonal m^2 + sigma_0
   double r2ref;    // |r|^2 at the last reliable update (or start)
   double rho_iter; // iterated |r|^2 just before the last reliable update
+  double rho_k;    // rho at the step length of the current iteration
+  int iter_k;      // iters at the step length of the current iteration
+  int pad_;
   int iters;       // Krylov iterations done
   int done;        // stopped (converged or out of iterations)
   int live;        // = !done, read by the D_oe kernel

@@ -11,6 +11,7 @@
 //   K3  r -= a (m2s p - D_eo t)        + FP64 partials of |r|^2   (fused)
 //   K4  (one workgroup) beta, beta_s, zeta history, per-shift freezing,
 //       convergence and iteration limits
+//       (on small lattices K2 and K4 are part of K3 and K5)
 //   K5  for every active shift: x_s += a_s p_s ; p_s = zeta_s r + beta_s p_s
 //                                      + FP64 partials of |p_0|^2
 // With deferred shift updates (multi-shift, window W > 1) K5 only forms the
@@ -47,6 +48,7 @@
 
 #include "dslash.h"
 #include "solver.h"
+#include "sysred.h"
 
 namespace lqcd {
 
@@ -56,6 +58,7 @@ int convert_links_async(const KGeom& k, const void* src, int sp, int sf, void* d
 namespace {
 
 constexpr int kVecBlock = 256;
+static_assert(kVecBlock == kSmallBlock, "the update kernels sum partials with small_sums");
 
 // --------------------------------------------------------------- kernels
 
@@ -242,6 +245,7 @@ __global__ void __launch_bounds__(kScalarThreads) k_sc_init(
 
 // K2: step length of the base system and the shifted zetas; one workgroup
 // per system (blockIdx.x), each reducing its own partials in fixed order.
+// (k_dslash_split does this itself on small lattices.)
 __global__ void __launch_bounds__(kScalarThreads) k_sc_alpha(SysState* __restrict__ st,
                                                               GlobalFlags* __restrict__ gf,
                                                               int nshift, const double* part_t,
@@ -251,132 +255,30 @@ __global__ void __launch_bounds__(kScalarThreads) k_sc_alpha(SysState* __restric
   const int j = blockIdx.x;
   double tt, pp;
   wg_sum2(part_t + int64_t(j) * nb_t, nb_t, part_p + int64_t(j) * nb_p, nb_p, lds, &tt, &pp);
-  if (threadIdx.x != 0) return;
-  SysState& S = st[j];
-  S.upd_any = 0;
-  S.restart = 0;
-  for (int s = 0; s < nshift; ++s) S.upd[s] = 0;
-  if (S.done) return;
-  const double pAp = S.m2s * pp + tt;  // <p, (m2s - D_eo D_oe) p>
-  S.pp = pp;
-  if (!(pAp > 0.0) || !finite_d(pAp)) {
-    S.err = 1;
-    S.done = 1;
-    S.live = 0;
-    gf->error = 1;
-    return;
-  }
-  const double a = S.rho / pAp;
-  S.a = a;
-  for (int s = 0; s < nshift; ++s) {
-    if (!S.active[s]) continue;
-    const double z = S.zeta[s], zo = S.zeta_old[s];
-    const double zn =
-        z * zo * S.a_old / (a * S.b_old * (zo - z) + zo * S.a_old * (1.0 + S.delta[s] * a));
-    S.zeta_new[s] = zn;
-    S.a_s[s] = a * zn / z;
-    S.upd[s] = 1;
-  }
-  S.upd_any = 1;
+  double step;
+  bool err;
+  const bool ok = cg_step(step_state(st[j]), tt, pp, &step, &err);
+  __syncthreads();  // every wave has read the state
+  store_step(st[j], gf, nshift, ok, err, step, pp, threadIdx.x);
 }
 
 // K4: beta, shifted betas, freezing, convergence; one workgroup per system.
-// The global flags are derived afterwards by k_sc_flags.  With deferred
-// shift updates (wc != nullptr) the whole workgroup then advances the window
-// coefficients of the updated shifts, one thread per coefficient:
-//   x_s += a_s p_s   ->  cx_s += a_s cp_s
-//   p_s  = zeta_s r + b_s p_s  ->  cp_s = b_s cp_s, cp_s[n+1] = zeta_s
-// where index n+1 is the residual after this iteration (ring slot n).
+// The global flags are derived at the end of a block of iterations by
+// k_sc_flags.  With deferred shift updates (wc != nullptr) the whole workgroup
+// then advances the window coefficients.
 __global__ void __launch_bounds__(kScalarThreads) k_sc_beta(SysState* __restrict__ st,
                                                              GlobalFlags* __restrict__ gf,
                                                              int nshift, const double* part_r,
-                                                             int nb_r, int max_iter,
-                                                             double rel_delta2, double sw2,
-                                                             int fp64, WinCoef* __restrict__ wc,
-                                                             int win) {
+                                                             int nb_r, const BetaArgs ba) {
   __shared__ double lds[kScalarThreads / 64];
-  __shared__ double sh_a[kMaxShift], sh_b[kMaxShift], sh_z[kMaxShift];
-  __shared__ int sh_u[kMaxShift];
-  __shared__ int sh_n;
+  __shared__ BetaShared sh;
   const int j = blockIdx.x;
   const double rr = wg_sum(part_r + int64_t(j) * nb_r, nb_r, lds);
-  if (threadIdx.x == 0) {
-    sh_n = -1;
-    SysState& S = st[j];
-    bool go = S.upd_any != 0;
-    if (go && !finite_d(rr)) {
-      S.err = 1;
-      S.done = 1;
-      S.live = 0;
-      S.upd_any = 0;
-      gf->error = 1;
-      go = false;
-    }
-    if (go && wc && S.wpos >= win) {  // the window was not flushed in time
-      S.err = 1;
-      S.done = 1;
-      S.live = 0;
-      S.upd_any = 0;
-      gf->error = 1;
-      go = false;
-    }
-    if (go) {
-      const double beta = rr / S.rho;
-      int nupd = 0;
-      for (int s = 0; s < nshift; ++s) {
-        sh_u[s] = S.upd[s];
-        if (!S.upd[s]) continue;
-        ++nupd;
-        const double ratio = S.zeta_new[s] / S.zeta[s];
-        S.b_s[s] = beta * ratio * ratio;
-        S.zeta_old[s] = S.zeta[s];
-        S.zeta[s] = S.zeta_new[s];
-        S.dirty[s] = 1;
-        S.wdirty[s] |= wc ? 1 : 0;
-        sh_a[s] = S.a_s[s];
-        sh_b[s] = S.b_s[s];
-        sh_z[s] = S.zeta[s];
-        if (S.zeta_new[s] * S.zeta_new[s] * rr <= S.target2) S.active[s] = 0;
-      }
-      S.a_old = S.a;
-      S.b_old = beta;
-      S.rho = rr;
-      S.iters += 1;
-      if (fp64) {
-        S.iters64 += 1;
-        S.upd64 += nupd;
-      } else {
-        S.upd32 += nupd;
-      }
-      if (rr < rel_delta2 * S.r2ref) gf->rel_req = 1;
-      if (rr <= sw2 * S.bnorm2) S.lowres = 1;
-      if (rr <= S.target2 || S.iters >= max_iter) {
-        S.done = 1;
-        S.live = 0;
-        S.conv = rr <= S.target2 ? 1 : 0;
-      }
-      if (wc) {
-        sh_n = S.wpos;
-        S.wpos += 1;
-      }
-    }
-  }
-  __syncthreads();
-  const int n = sh_n;
-  if (n < 0) return;
-  const int s = threadIdx.x / kWinRow, q = threadIdx.x % kWinRow;
-  if (s >= nshift || !sh_u[s]) return;
-  WinCoef& C = wc[j];
-  if (q <= n) {
-    const double cp = C.cp[s][q];
-    C.cx[s][q] = fma(sh_a[s], cp, C.cx[s][q]);
-    C.cp[s][q] = sh_b[s] * cp;
-  } else if (q == n + 1) {
-    C.cp[s][q] = sh_z[s];
-  }
+  store_beta(st[j], gf, nshift, rr, ba, ba.wc ? ba.wc + j : nullptr, sh);
 }
 
-// all_done / phase_done over every system
+// all_done / phase_done over every system (for the host: within a block of
+// iterations every kernel goes by the systems' own live flags)
 __global__ void k_sc_flags(const SysState* __restrict__ st, GlobalFlags* __restrict__ gf,
                            int nsys) {
   if (threadIdx.x != 0) return;
@@ -389,27 +291,78 @@ __global__ void k_sc_flags(const SysState* __restrict__ st, GlobalFlags* __restr
   gf->phase_done = phase_done;
 }
 
-// K5: x_s += a_s p_s ; p_s = zeta_s r + beta_s p_s for the shifts updated this iteration
-template <typename RI, typename RX>
-__global__ void __launch_bounds__(kVecBlock) k_ms_update(const SysState* __restrict__ st,
+// In the update kernels below FB (fused beta, small lattices) does K4's work as
+// well: every workgroup sums the partials of |r|^2 (nb_r of them, at most
+// kFusedPartials) and takes beta from them, and one more of each system,
+// besides the nb that update, stores the state.  The coefficients of the base
+// direction then come from what the step length left in the state: zeta_0 = 1
+// before and after.  16^4, 8 shifts: 4.7 us instead of 3.9 and 5.1 us for K4; a
+// whole mixed iteration 16.5 us instead of 34, an FP64 one 25 instead of 36.
+template <int K>
+struct FusedBeta {
+  double red[K][kScalarThreads / 64];
+  BetaShared sh;
+};
+
+struct BaseStep {
+  bool go;
+  double zs, bs;  // p = zs r + bs p  (fused: bs = |r|^2 / bs, once |r|^2 is known)
+  int slot;       // ring slot of the new residual (before % R)
+};
+
+__device__ __forceinline__ BaseStep base_step(const SysState& S, int base, bool fused) {
+  if (fused) return BaseStep{S.upd_any != 0, S.zeta_new[base], S.rho_k, S.iter_k + 1};
+  return BaseStep{S.upd_any != 0, S.zeta[base], S.b_s[base], S.iters};
+}
+
+__device__ __forceinline__ void finish_step(BaseStep& u, double rr) {
+  u.go = u.go && finite_d(rr);
+  u.bs = rr / u.bs;
+}
+
+// K5: x_s += a_s p_s ; p_s = zeta_s r + beta_s p_s for the shifts updated this
+// iteration (FB: a single shift)
+template <typename RI, typename RX, bool FB>
+__global__ void __launch_bounds__(kVecBlock) k_ms_update(SysState* __restrict__ st,
+                                                         GlobalFlags* __restrict__ gf,
                                                          const cplx<RI>* __restrict__ r,
                                                          cplx<RI>* __restrict__ p,
                                                          cplx<RX>* __restrict__ x, int nshift,
                                                          int base, int Vh,
+                                                         const double* __restrict__ part_r,
+                                                         int nb_r, int nb, const BetaArgs ba,
                                                          double* __restrict__ part) {
   __shared__ double lds[kVecBlock / 64];
   const int j = blockIdx.y;
-  const SysState& S = st[j];
-  if (!S.upd_any) return;
+  SysState& S = st[j];
   const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  double pn = 0.0;
-  if (h < Vh) {
-    cplx<RI> rv[3];
+  BaseStep u = base_step(S, base, FB);
+  if (!FB && !u.go) return;
+  cplx<RI> rv[3];
+  if (h < Vh)
 #pragma unroll
     for (int c = 0; c < 3; ++c) rv[c] = r[(int64_t(j) * 3 + c) * Vh + h];
+  if constexpr (FB) {  // the partials of |r|^2, summed while r is on its way
+    __shared__ FusedBeta<1> fb;
+    const double* pr[1] = {part_r + int64_t(j) * nb_r};
+    const int nr[1] = {nb_r};
+    SmallSums<1> ps;
+    ps.load(pr, nr);
+    ps.reduce(fb.red);
+    __syncthreads();
+    const double rr = ps.sum(fb.red[0]);
+    if (int(blockIdx.x) == nb) {
+      store_beta(S, gf, nshift, rr, ba, nullptr, fb.sh);
+      return;
+    }
+    finish_step(u, rr);
+    if (!u.go) return;
+  }
+  double pn = 0.0;
+  if (h < Vh) {
     for (int s = 0; s < nshift; ++s) {
-      if (!S.upd[s]) continue;
-      const RI as = RI(S.a_s[s]), zs = RI(S.zeta[s]), bs = RI(S.b_s[s]);
+      if (!FB && !S.upd[s]) continue;
+      const RI as = RI(S.a_s[s]), zs = RI(FB ? u.zs : S.zeta[s]), bs = RI(FB ? u.bs : S.b_s[s]);
       const int64_t o = (int64_t(j) * nshift + s) * 3 * Vh + h;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -426,86 +379,136 @@ __global__ void __launch_bounds__(kVecBlock) k_ms_update(const SysState* __restr
     }
   }
   pn = block_sum(pn, lds);
-  if (threadIdx.x == 0) part[int64_t(j) * gridDim.x + blockIdx.x] = pn;
+  if (threadIdx.x == 0) part[int64_t(j) * nb + blockIdx.x] = pn;
 }
 
 // K5 with deferred shift updates: p = zeta_0 r + beta_0 p for the base
 // direction only (zeta_0 = 1); r is the new residual, which the fused D_eo
 // update wrote into ring slot iters % R (R = window + 1 slots, so a window's
 // residuals stay in place until it is flushed); partials of |p|^2.
-template <typename RI>
-__global__ void __launch_bounds__(kVecBlock) k_base_update(const SysState* __restrict__ st,
+template <typename RI, bool FB>
+__global__ void __launch_bounds__(kVecBlock) k_base_update(SysState* __restrict__ st,
+                                                           GlobalFlags* __restrict__ gf,
                                                            const cplx<RI>* __restrict__ r,
                                                            int R, cplx<RI>* __restrict__ pc,
-                                                           int base, int Vh,
+                                                           int nshift, int base, int Vh,
+                                                           const double* __restrict__ part_r,
+                                                           int nb_r, int nb, const BetaArgs ba,
                                                            double* __restrict__ part) {
   __shared__ double lds[kVecBlock / 64];
   const int j = blockIdx.y;
-  const SysState& S = st[j];
-  if (!S.upd_any) return;
+  SysState& S = st[j];
+  BaseStep u = base_step(S, base, FB);
+  if (!FB && !u.go) return;
   const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t rs = int64_t(j) * R + S.iters % R;
-  double pn = 0.0;
-  if (h < Vh) {
-    const RI zs = RI(S.zeta[base]), bs = RI(S.b_s[base]);
+  const int64_t rs = int64_t(j) * R + u.slot % R;
+  cplx<RI> rv[3], pv[3];
+  if (h < Vh)
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const int64_t i = (int64_t(j) * 3 + c) * Vh + h;
-      const cplx<RI> rv = r[(rs * 3 + c) * Vh + h];
-      cplx<RI> pv = pc[i];
-      pv.x = fma(zs, rv.x, bs * pv.x);
-      pv.y = fma(zs, rv.y, bs * pv.y);
-      pc[i] = pv;
-      pn += cnorm2<RI>(pv);
+      rv[c] = r[(rs * 3 + c) * Vh + h];
+      pv[c] = pc[(int64_t(j) * 3 + c) * Vh + h];
+    }
+  if constexpr (FB) {  // the partials of |r|^2, summed while r and p are on their way
+    __shared__ FusedBeta<1> fb;
+    const double* pr[1] = {part_r + int64_t(j) * nb_r};
+    const int nr[1] = {nb_r};
+    SmallSums<1> ps;
+    ps.load(pr, nr);
+    ps.reduce(fb.red);
+    __syncthreads();
+    const double rr = ps.sum(fb.red[0]);
+    if (int(blockIdx.x) == nb) {
+      store_beta(S, gf, nshift, rr, ba, ba.wc + j, fb.sh);
+      return;
+    }
+    finish_step(u, rr);
+    if (!u.go) return;
+  }
+  double pn = 0.0;
+  if (h < Vh) {
+    const RI zs = RI(u.zs), bs = RI(u.bs);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      pv[c].x = fma(zs, rv[c].x, bs * pv[c].x);
+      pv[c].y = fma(zs, rv[c].y, bs * pv[c].y);
+      pc[(int64_t(j) * 3 + c) * Vh + h] = pv[c];
+      pn += cnorm2<RI>(pv[c]);
     }
   }
   pn = block_sum(pn, lds);
-  if (threadIdx.x == 0) part[int64_t(j) * gridDim.x + blockIdx.x] = pn;
+  if (threadIdx.x == 0) part[int64_t(j) * nb + blockIdx.x] = pn;
 }
 
 // k_base_update<float> for base directions stored in pairs (systems 2q and
 // 2q + 1 interleaved, blockIdx.y = q): one thread updates a site of both with
 // 16-byte accesses, the same arithmetic per system and the same partials; a
 // system that does not update keeps its values bit for bit.
+template <bool FB>
 __global__ void __launch_bounds__(kVecBlock) k_base_update_pairs(
-    const SysState* __restrict__ st, const float2* __restrict__ r, int R,
-    float4* __restrict__ pc, int base, int Vh, double* __restrict__ part) {
+    SysState* __restrict__ st, GlobalFlags* __restrict__ gf, const float2* __restrict__ r, int R,
+    float4* __restrict__ pc, int nshift, int base, int Vh, const double* __restrict__ part_r,
+    int nb_r, int nb, const BetaArgs ba, double* __restrict__ part) {
   __shared__ double lds0[kVecBlock / 64], lds1[kVecBlock / 64];
   const int j0 = 2 * blockIdx.y, j1 = j0 + 1;
-  const SysState& S0 = st[j0];
-  const SysState& S1 = st[j1];
-  const bool u0 = S0.upd_any != 0, u1 = S1.upd_any != 0;
-  if (!u0 && !u1) return;
+  SysState& S0 = st[j0];
+  SysState& S1 = st[j1];
+  BaseStep u0 = base_step(S0, base, FB), u1 = base_step(S1, base, FB);
+  if (!FB && !u0.go && !u1.go) return;
   const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t rs0 = int64_t(j0) * R + S0.iters % R, rs1 = int64_t(j1) * R + S1.iters % R;
-  double pn0 = 0.0, pn1 = 0.0;
-  if (h < Vh) {
-    const float zs0 = float(S0.zeta[base]), bs0 = float(S0.b_s[base]);
-    const float zs1 = float(S1.zeta[base]), bs1 = float(S1.b_s[base]);
+  const int64_t rs0 = int64_t(j0) * R + u0.slot % R, rs1 = int64_t(j1) * R + u1.slot % R;
+  float2 rv0[3], rv1[3];
+  float4 pv[3];
+  if (h < Vh)
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      const int64_t i = (int64_t(blockIdx.y) * 3 + c) * Vh + h;  // float4 units
-      const float2 rv0 = r[(rs0 * 3 + c) * Vh + h];
-      const float2 rv1 = r[(rs1 * 3 + c) * Vh + h];
-      float4 pv = pc[i];
-      if (u0) {
-        pv.x = fma(zs0, rv0.x, bs0 * pv.x);
-        pv.y = fma(zs0, rv0.y, bs0 * pv.y);
-        pn0 += cnorm2<float>(make_float2(pv.x, pv.y));
+      rv0[c] = r[(rs0 * 3 + c) * Vh + h];
+      rv1[c] = r[(rs1 * 3 + c) * Vh + h];
+      pv[c] = pc[(int64_t(blockIdx.y) * 3 + c) * Vh + h];  // float4 units
+    }
+  if constexpr (FB) {
+    __shared__ FusedBeta<2> fb;
+    const double* pr[2] = {part_r + int64_t(j0) * nb_r, part_r + int64_t(j1) * nb_r};
+    const int nr[2] = {nb_r, nb_r};
+    SmallSums<2> ps;
+    ps.load(pr, nr);
+    ps.reduce(fb.red);
+    __syncthreads();
+    const double rr0 = ps.sum(fb.red[0]), rr1 = ps.sum(fb.red[1]);
+    if (int(blockIdx.x) == nb) {
+      store_beta(S0, gf, nshift, rr0, ba, ba.wc + j0, fb.sh);
+      __syncthreads();
+      store_beta(S1, gf, nshift, rr1, ba, ba.wc + j1, fb.sh);
+      return;
+    }
+    finish_step(u0, rr0);
+    finish_step(u1, rr1);
+    if (!u0.go && !u1.go) return;
+  }
+  double pn0 = 0.0, pn1 = 0.0;
+  if (h < Vh) {
+    const float zs0 = float(u0.zs), bs0 = float(u0.bs);
+    const float zs1 = float(u1.zs), bs1 = float(u1.bs);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (u0.go) {
+        pv[c].x = fma(zs0, rv0[c].x, bs0 * pv[c].x);
+        pv[c].y = fma(zs0, rv0[c].y, bs0 * pv[c].y);
+        pn0 += cnorm2<float>(make_float2(pv[c].x, pv[c].y));
       }
-      if (u1) {
-        pv.z = fma(zs1, rv1.x, bs1 * pv.z);
-        pv.w = fma(zs1, rv1.y, bs1 * pv.w);
-        pn1 += cnorm2<float>(make_float2(pv.z, pv.w));
+      if (u1.go) {
+        pv[c].z = fma(zs1, rv1[c].x, bs1 * pv[c].z);
+        pv[c].w = fma(zs1, rv1[c].y, bs1 * pv[c].w);
+        pn1 += cnorm2<float>(make_float2(pv[c].z, pv[c].w));
       }
-      pc[i] = pv;
+      pc[(int64_t(blockIdx.y) * 3 + c) * Vh + h] = pv[c];
     }
   }
   pn0 = block_sum(pn0, lds0);
   pn1 = block_sum(pn1, lds1);
   if (threadIdx.x == 0) {
-    if (u0) part[int64_t(j0) * gridDim.x + blockIdx.x] = pn0;
-    if (u1) part[int64_t(j1) * gridDim.x + blockIdx.x] = pn1;
+    if (u0.go) part[int64_t(j0) * nb + blockIdx.x] = pn0;
+    if (u1.go) part[int64_t(j1) * nb + blockIdx.x] = pn1;
   }
 }
 
@@ -990,6 +993,7 @@ struct Phase {
   size_t r = 0, t = 0, p = 0;  // workspace offsets of r, t (odd), p_s
   size_t pc = 0;               // base direction (deferred shift updates)
   int pairs = 0;               // pc and t hold the systems in interleaved pairs (FP32)
+  bool fused = false;          // scalars computed inside D_eo and the update (small lattices)
   void* x = nullptr;           // solution accumulator: FP64 solutions or FP32 partial sums
   DslashCfg c_oe, c_eo;
   int nb_oe = 0, nb_eo = 0;
@@ -1018,6 +1022,14 @@ bool is_mixed(const Ctx& c) { return c.iprec == LQCD_F32; }
 // other (for comparisons); unset or any other value: pairs wherever they apply.
 bool rhs_pairs_enabled() {
   const char* e = std::getenv("LQCD_RHS_PAIRS");
+  return !(e && e[0] == '0');
+}
+
+// LQCD_FUSED_SCALARS=0 keeps the scalars in kernels of their own (for
+// comparisons: the bits are the same); unset or any other value: inside the
+// stencil and the update wherever that applies.
+bool fused_scalars_enabled() {
+  const char* e = std::getenv("LQCD_FUSED_SCALARS");
   return !(e && e[0] == '0');
 }
 
@@ -1084,7 +1096,10 @@ int launch_flush(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s) {
   return LQCD_OK;
 }
 
-int launch_iteration(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s, bool flush) {
+// One iteration; flush: its window of deferred shift updates ends here; last: the
+// host reads the flags next.
+int launch_iteration(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s, bool flush,
+                     bool last) {
   SysState* st = c.at<SysState>(c.L.st);
   GlobalFlags* gf = c.at<GlobalFlags>(c.L.gf);
   const int64_t vs = vstride(c);
@@ -1108,9 +1123,11 @@ int launch_iteration(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s
   if ((rc = dslash_launch(d1, ph.c_oe, s))) return rc;
   timing_end(ev, s, "dslash_oe" + tag);
   // K2
-  hipLaunchKernelGGL(k_sc_alpha, dim3(k.nsys), dim3(kScalarThreads), 0, s, st, gf, k.nshift,
-                     c.at<double>(c.L.pt), ph.nb_oe, c.at<double>(c.L.pp), k.nbv);
-  LQCD_LAUNCH_CHECK();
+  if (!ph.fused) {
+    hipLaunchKernelGGL(k_sc_alpha, dim3(k.nsys), dim3(kScalarThreads), 0, s, st, gf, k.nshift,
+                       c.at<double>(c.L.pt), ph.nb_oe, c.at<double>(c.L.pp), k.nbv);
+    LQCD_LAUNCH_CHECK();
+  }
   // K3: r -= a (m2s p - D_eo t)
   DslashCall d3 = phase_call(c, k, ph, 0);
   d3.mode = DM_CG;
@@ -1130,8 +1147,17 @@ int launch_iteration(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s
   d3.m2s_stride = kStateStrideD;
   d3.alpha = &st->a;
   d3.alpha_stride = kStateStrideD;
-  d3.live = &st->upd_any;
+  d3.live = ph.fused ? &st->live : &st->upd_any;
   d3.live_stride = kStateStrideI;
+  if (ph.fused) {
+    d3.sys = st;
+    d3.flags = gf;
+    d3.nshift = k.nshift;
+    d3.step_t = c.at<double>(c.L.pt);
+    d3.step_nt = ph.nb_oe;
+    d3.step_p = c.at<double>(c.L.pp);
+    d3.step_np = k.nbv;
+  }
   d3.halt = &gf->all_done;
   d3.partials = c.at<double>(c.L.pr);
   d3.rev = 1;  // against D_oe's order: the last t it wrote is read first (MALL hits)
@@ -1139,43 +1165,64 @@ int launch_iteration(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s
   if ((rc = dslash_launch(d3, ph.c_eo, s))) return rc;
   timing_end(ev, s, "dslash_eo_cg" + tag);
   // K4
-  hipLaunchKernelGGL(k_sc_beta, dim3(k.nsys), dim3(kScalarThreads), 0, s, st, gf, k.nshift,
-                     c.at<double>(c.L.pr), ph.nb_eo, c.p.max_iter, ph.rel_d2, ph.sw2,
-                     ph.prec == LQCD_F64 ? 1 : 0, win ? c.at<WinCoef>(c.L.wc) : nullptr, k.win);
-  LQCD_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_sc_flags, dim3(1), dim3(64), 0, s, st, gf, k.nsys);
-  LQCD_LAUNCH_CHECK();
-  // K5
-  const dim3 grid(k.nbv, k.nsys);
-  if (win) {
-    ev = timing_begin(s);
-    if (ph.pairs)
-      hipLaunchKernelGGL(k_base_update_pairs, dim3(k.nbv, k.nsys / 2), dim3(kVecBlock), 0, s, st,
-                         c.at<const float2>(ph.r), rslots(k), c.at<float4>(ph.pc), k.base,
-                         c.g.Vh, c.at<double>(c.L.pp));
-    else if (ph.prec == LQCD_F32)
-      hipLaunchKernelGGL(k_base_update<float>, grid, dim3(kVecBlock), 0, s, st,
-                         c.at<const float2>(ph.r), rslots(k), c.at<float2>(ph.pc), k.base,
-                         c.g.Vh, c.at<double>(c.L.pp));
-    else
-      hipLaunchKernelGGL(k_base_update<double>, grid, dim3(kVecBlock), 0, s, st,
-                         c.at<const double2>(ph.r), rslots(k), c.at<double2>(ph.pc), k.base,
-                         c.g.Vh, c.at<double>(c.L.pp));
+  BetaArgs ba;
+  ba.max_iter = c.p.max_iter;
+  ba.rel_delta2 = ph.rel_d2;
+  ba.sw2 = ph.sw2;
+  ba.fp64 = ph.prec == LQCD_F64 ? 1 : 0;
+  ba.wc = win ? c.at<WinCoef>(c.L.wc) : nullptr;
+  ba.win = k.win;
+  const double* part_r = c.at<double>(c.L.pr);
+  if (!ph.fused) {
+    hipLaunchKernelGGL(k_sc_beta, dim3(k.nsys), dim3(kScalarThreads), 0, s, st, gf, k.nshift,
+                       part_r, ph.nb_eo, ba);
     LQCD_LAUNCH_CHECK();
-    timing_end(ev, s, "base_update" + tag);
-    return flush ? launch_flush(c, k, ph, s) : LQCD_OK;
   }
+  // K5
+  const int nbx = ph.fused ? k.nbv + 1 : k.nbv;  // one more workgroup stores the state
+  const dim3 grid(nbx, k.nsys);
   ev = timing_begin(s);
-  if (ph.prec == LQCD_F32)
-    hipLaunchKernelGGL((k_ms_update<float, float>), grid, dim3(kVecBlock), 0, s, st,
-                       c.at<const float2>(ph.r), c.at<float2>(ph.p), (float2*)ph.x, k.nshift,
-                       k.base, c.g.Vh, c.at<double>(c.L.pp));
-  else
-    hipLaunchKernelGGL((k_ms_update<double, double>), grid, dim3(kVecBlock), 0, s, st,
-                       c.at<const double2>(ph.r), c.at<double2>(ph.p), (double2*)ph.x, k.nshift,
-                       k.base, c.g.Vh, c.at<double>(c.L.pp));
+#define LQCD_UPD(KERNEL, GRID, ...)                                                              \
+  hipLaunchKernelGGL((KERNEL), GRID, dim3(kVecBlock), 0, s, st, gf, __VA_ARGS__, k.nshift,       \
+                     k.base, c.g.Vh, part_r, ph.nb_eo, k.nbv, ba, c.at<double>(c.L.pp))
+#define LQCD_BASE(RI, FB)                                                                        \
+  LQCD_UPD(LQCD_ARG(k_base_update<RI, FB>), grid, c.at<const cplx<RI>>(ph.r), rslots(k),         \
+           c.at<cplx<RI>>(ph.pc))
+#define LQCD_MS(RI, FB)                                                                          \
+  LQCD_UPD(LQCD_ARG(k_ms_update<RI, RI, FB>), grid, c.at<const cplx<RI>>(ph.r),                  \
+           c.at<cplx<RI>>(ph.p), static_cast<cplx<RI>*>(ph.x))
+#define LQCD_ARG(...) __VA_ARGS__
+  const bool f32 = ph.prec == LQCD_F32;
+  if (win && ph.pairs) {
+    const dim3 gp(nbx, k.nsys / 2);
+    if (ph.fused)
+      LQCD_UPD(k_base_update_pairs<true>, gp, c.at<const float2>(ph.r), rslots(k),
+               c.at<float4>(ph.pc));
+    else
+      LQCD_UPD(k_base_update_pairs<false>, gp, c.at<const float2>(ph.r), rslots(k),
+               c.at<float4>(ph.pc));
+  } else if (win) {
+    if (f32 && ph.fused) LQCD_BASE(float, true);
+    else if (f32) LQCD_BASE(float, false);
+    else if (ph.fused) LQCD_BASE(double, true);
+    else LQCD_BASE(double, false);
+  } else {
+    if (f32 && ph.fused) LQCD_MS(float, true);
+    else if (f32) LQCD_MS(float, false);
+    else if (ph.fused) LQCD_MS(double, true);
+    else LQCD_MS(double, false);
+  }
+#undef LQCD_ARG
+#undef LQCD_MS
+#undef LQCD_BASE
+#undef LQCD_UPD
   LQCD_LAUNCH_CHECK();
-  timing_end(ev, s, "ms_update" + tag);
+  timing_end(ev, s, (win ? "base_update" : "ms_update") + tag);
+  if (flush && win && (rc = launch_flush(c, k, ph, s))) return rc;
+  if (last) {
+    hipLaunchKernelGGL(k_sc_flags, dim3(1), dim3(64), 0, s, st, gf, k.nsys);
+    LQCD_LAUNCH_CHECK();
+  }
   return LQCD_OK;
 }
 
@@ -1263,6 +1310,7 @@ std::string graph_key(const Ctx& c, const Core& k, const Phase& ph) {
   add(&ph.p, sizeof(size_t));
   add(&ph.pc, sizeof(size_t));
   add(&ph.pairs, sizeof(int));
+  add(&ph.fused, sizeof(bool));
   add(&ph.x, sizeof(void*));
   add(&ph.c_oe, sizeof(DslashCfg));
   add(&ph.c_eo, sizeof(DslashCfg));
@@ -1284,7 +1332,7 @@ int iteration_graph(const Ctx& c, const Core& k, const Phase& ph, hipGraphExec_t
   LQCD_HIP_TRY(hipStreamBeginCapture(gl.cap, hipStreamCaptureModeThreadLocal));
   int rc = LQCD_OK;
   for (int i = 0; i < k.poll && rc == LQCD_OK; ++i)
-    rc = launch_iteration(c, k, ph, gl.cap, (i + 1) % k.win == 0);
+    rc = launch_iteration(c, k, ph, gl.cap, (i + 1) % k.win == 0, i + 1 == k.poll);
   hipGraph_t graph = nullptr;
   const hipError_t e = hipStreamEndCapture(gl.cap, &graph);
   if (rc != LQCD_OK) {
@@ -1341,6 +1389,16 @@ int read_flags(const Ctx& c, GlobalFlags* host) {
   return LQCD_OK;
 }
 
+// Whether the iteration computes its scalars inside the stencil and the update
+// (three launches) instead of in one-workgroup kernels between them (five): the
+// D_eo kernel must be the one that can, the partials must fit its one-pass
+// sum, and only the base direction may need a new coefficient in the update.
+bool fused_scalars(const Ctx& c, const Core& k, const Phase& ph) {
+  const int nbv = (c.g.Vh + kVecBlock - 1) / kVecBlock;
+  return ph.c_eo.sp == 1 && fused_scalars_enabled() && (k.win > 1 || k.nshift == 1) && ph.nb_oe <= kFusedPartials &&
+         ph.nb_eo <= kFusedPartials && nbv <= kFusedPartials;
+}
+
 int tune_phase(const Ctx& c, const Core& k, Phase& ph) {
   int rc;
   DslashCall t = phase_call(c, k, ph, 1);
@@ -1351,6 +1409,7 @@ int tune_phase(const Ctx& c, const Core& k, Phase& ph) {
   if ((rc = dslash_tuned(t, c.p.rhs_block, c.s, &ph.c_eo))) return rc;
   ph.nb_oe = dslash_nblocks(c.g, ph.c_oe);
   ph.nb_eo = dslash_nblocks(c.g, ph.c_eo);
+  ph.fused = fused_scalars(c, k, ph);
   return LQCD_OK;
 }
 
@@ -1417,7 +1476,8 @@ int run_phase(const Ctx& c, const Core& k, const Phase& ph, bool reliable, bool 
       LQCD_HIP_TRY(hipGraphLaunch(exec, c.s));
     } else {
       for (int i = 0; i < k.poll; ++i)
-        if ((rc = launch_iteration(c, k, ph, c.s, (i + 1) % k.win == 0))) return rc;
+        if ((rc = launch_iteration(c, k, ph, c.s, (i + 1) % k.win == 0, i + 1 == k.poll)))
+          return rc;
     }
     *iters_run += k.poll;
     since_rel += k.poll;

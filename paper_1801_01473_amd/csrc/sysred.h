@@ -1,0 +1,221 @@
+// Reductions of block partials inside kernels of any workgroup size, and the
+// step length of CG computed from them.
+#pragma once
+
+#include "common.h"
+#include "solver.h"
+
+namespace lqcd {
+
+// Partial counts up to this fit the one-pass reduction below.
+constexpr int kFusedPartials = kScalarThreads;
+
+// The sums of K arrays of n[k] <= kScalarThreads doubles by a workgroup of 256
+// threads, in the order in which a workgroup of kScalarThreads threads (wg_sum)
+// adds them -- 16 groups of 64, a butterfly in each, the groups in order -- so
+// with the same bits.  All loads are issued before the first butterfly.  Every
+// thread gets the results.
+constexpr int kSmallBlock = 256;
+
+template <int K>
+struct SmallSums {
+  static constexpr int W = kScalarThreads / 64, NW = kSmallBlock / 64, M = W / NW;
+  double v[K][M];
+  // issues the loads
+  __device__ __forceinline__ void load(const double* const (&p)[K], const int (&n)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int i = (int(threadIdx.x >> 6) + NW * m) * 64 + int(threadIdx.x & 63);
+        v[k][m] = i < n[k] ? p[k][i] : 0.0;
+      }
+  }
+  // sums groups of 64 into LDS; a barrier goes between this and sum()
+  __device__ __forceinline__ void reduce(double (&lds)[K][W]) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int m = 0; m < M; ++m) v[k][m] += __shfl_xor(v[k][m], off, 64);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int m = 0; m < M; ++m) lds[k][(threadIdx.x >> 6) + NW * m] = v[k][m];
+  }
+  __device__ __forceinline__ static double sum(const double (&lds)[W]) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) s += lds[w];
+    return s;
+  }
+};
+
+// What the step length depends on; read with the other flags of a kernel.
+struct StepState {
+  double rho, m2s;
+  int done;
+};
+
+__device__ __forceinline__ StepState step_state(const SysState& S) {
+  return StepState{S.rho, S.m2s, S.done};
+}
+
+// Step length of the base system from |p|^2 and |D_oe p|^2; false: the system
+// is finished, or the curvature <p, A p> is not a positive number (err).
+__device__ __forceinline__ bool cg_step(const StepState& S, double tt, double pp, double* a,
+                                        bool* err) {
+  *err = false;
+  *a = 0.0;
+  if (S.done) return false;
+  const double pAp = S.m2s * pp + tt;
+  if (!(pAp > 0.0) || !(pAp == pAp && fabs(pAp) <= 1.7e308)) {
+    *err = true;
+    return false;
+  }
+  *a = S.rho / pAp;
+  return true;
+}
+
+// The state after the step length is known, by kMaxShift threads of one
+// wavefront: s in [0, kMaxShift) is the thread's number (others do nothing) and
+// the shift it advances.
+__device__ __forceinline__ void store_step(SysState& S, GlobalFlags* gf, int nshift, bool ok,
+                                           bool err, double a, double pp, int s) {
+  if (s < 0 || s >= kMaxShift) return;
+  // values another thread stores below are read before (one wavefront)
+  const double rho = S.rho, a_old = S.a_old, b_old = S.b_old;
+  const int iters = S.iters;
+  if (s < nshift) {
+    const bool up = ok && S.active[s];
+    S.upd[s] = up ? 1 : 0;
+    if (up) {
+      const double z = S.zeta[s], zo = S.zeta_old[s];
+      const double zn =
+          z * zo * a_old / (a * b_old * (zo - z) + zo * a_old * (1.0 + S.delta[s] * a));
+      S.zeta_new[s] = zn;
+      S.a_s[s] = a * zn / z;
+    }
+  }
+  if (s != 0) return;
+  S.restart = 0;
+  S.upd_any = ok ? 1 : 0;
+  S.rho_k = rho;
+  S.iter_k = iters;
+  if (ok || err) S.pp = pp;
+  if (ok) S.a = a;
+  if (err) {
+    S.err = 1;
+    S.done = 1;
+    S.live = 0;
+    gf->error = 1;
+  }
+}
+
+// The state after the residual norm rr is known, by a whole workgroup: thread s
+// advances shift s, then every thread its share of the window coefficients
+// (wc, deferred shift updates):
+//   x_s += a_s p_s   ->  cx_s += a_s cp_s
+//   p_s  = zeta_s r + b_s p_s  ->  cp_s = b_s cp_s, cp_s[n+1] = zeta_s
+// where index n+1 is the residual after this iteration (ring slot n).  S.rho_k,
+// S.iter_k, S.zeta_new and (unless rr is not finite, which every workgroup sees)
+// S.upd_any stay as the step length left them, so other workgroups of the same
+// launch may read those.
+struct BetaArgs {
+  int max_iter = 0;
+  double rel_delta2 = 0.0;  // reliable-update trigger
+  double sw2 = 0.0;         // FP64 -> FP32 switch level
+  int fp64 = 0;             // arithmetic of this phase
+  WinCoef* wc = nullptr;    // window coefficients of every system, or none
+  int win = 1;
+};
+
+struct BetaShared {
+  double a[kMaxShift], b[kMaxShift], z[kMaxShift];
+  int u[kMaxShift];
+  int n;
+};
+
+__device__ __forceinline__ void store_beta(SysState& S, GlobalFlags* gf, int nshift, double rr,
+                                           const BetaArgs& ba, WinCoef* wc, BetaShared& sh) {
+  const int s = threadIdx.x;
+  if (s < 64) {  // one wavefront: its reads of the state come before its stores
+    bool go = S.upd_any != 0;
+    const int wpos = S.wpos;
+    const bool bad = go && (!(rr == rr && fabs(rr) <= 1.7e308) || (wc && wpos >= ba.win));
+    if (bad) go = false;
+    const double rho = S.rho_k, a_step = S.a;
+    const double beta = go ? rr / rho : 0.0;
+    bool up = false;
+    if (go && s < nshift) {
+      up = S.upd[s] != 0;
+      sh.u[s] = up ? 1 : 0;
+      if (up) {
+        const double zn = S.zeta_new[s], z = S.zeta[s];
+        const double ratio = zn / z;
+        const double bs = beta * ratio * ratio;
+        S.b_s[s] = bs;
+        S.zeta_old[s] = z;
+        S.zeta[s] = zn;
+        S.dirty[s] = 1;
+        if (wc) S.wdirty[s] = 1;
+        sh.a[s] = S.a_s[s];
+        sh.b[s] = bs;
+        sh.z[s] = zn;
+        if (zn * zn * rr <= S.target2) S.active[s] = 0;
+      }
+    }
+    const int nupd = __popcll(__ballot(up));
+    if (s == 0) {
+      sh.n = -1;
+      if (bad) {
+        S.err = 1;
+        S.done = 1;
+        S.live = 0;
+        S.upd_any = 0;
+        gf->error = 1;
+      }
+      if (go) {
+        S.a_old = a_step;
+        S.b_old = beta;
+        S.rho = rr;
+        S.iters += 1;
+        if (ba.fp64) {
+          S.iters64 += 1;
+          S.upd64 += nupd;
+        } else {
+          S.upd32 += nupd;
+        }
+        if (rr < ba.rel_delta2 * S.r2ref) gf->rel_req = 1;
+        if (rr <= ba.sw2 * S.bnorm2) S.lowres = 1;
+        if (rr <= S.target2 || S.iters >= ba.max_iter) {
+          S.done = 1;
+          S.live = 0;
+          S.conv = rr <= S.target2 ? 1 : 0;
+        }
+        if (wc) {
+          sh.n = wpos;
+          S.wpos = wpos + 1;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  const int n = sh.n;
+  if (n < 0) return;
+  for (int i = threadIdx.x; i < nshift * kWinRow; i += blockDim.x) {
+    const int k = i / kWinRow, q = i % kWinRow;
+    if (!sh.u[k]) continue;
+    if (q <= n) {
+      const double cp = wc->cp[k][q];
+      wc->cx[k][q] = fma(sh.a[k], cp, wc->cx[k][q]);
+      wc->cp[k][q] = sh.b[k] * cp;
+    } else if (q == n + 1) {
+      wc->cp[k][q] = sh.z[k];
+    }
+  }
+}
+
+}  // namespace lqcd
