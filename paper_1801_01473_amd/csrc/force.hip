@@ -11,13 +11,22 @@
 // or the backward link of x+mu (x even), so one odd site y owns the eight
 // links of its star and writes each of them once: no atomics.
 //
-// Work split: four lanes per odd site, lane mu owns the links (y, mu) and
-// (y - mu, mu).  For each (pseudofermion, shift) pair the lane computes the
-// direction-mu part of chi(y) = (D_oe X)(y) with its two links, the quad adds
-// the four parts with two butterfly shuffles (same order in every lane), and
-// each lane adds the two outer products into its two 3x3 accumulators.  chi is
-// never written to memory.  At the end the lane projects U M to the traceless
-// anti-Hermitian part (mode 0) or writes M^dag (mode 1, torch's gradient).
+// Work split: a workgroup takes 64 odd sites and wave mu owns their links (y, mu)
+// and (y - mu, mu).  For each (pseudofermion, shift) pair a lane computes the
+// direction-mu part of chi(y) = (D_oe X)(y) with its two links, the four parts
+// are added through LDS (same order in every wave), and the lane adds the two
+// outer products into its two 3x3 accumulators.  chi is never written to memory.
+// At the end the lane projects U M to the traceless anti-Hermitian part (mode 0)
+// or writes M^dag (mode 1, torch's gradient).
+//
+// At 32^3 x 48 with 48 pairs the kernel takes 1.62 ms (1.74 ms with four lanes
+// of one wave per site and two shuffles per pair): 464 M vector instructions
+// keep the FP64 units busy 55-65 % of the time at the 1.9-2.0 GHz that the card
+// holds under them, 15 GB of loads go through L1 (11 GB from L2, 4.9 GB from
+// memory against 2.7 GB that must be read).  With every X read from L2 it would
+// take 1.42 ms.  Two lanes per link at twice the waves (1.67 ms), loads two pairs
+// ahead (1.62 ms), the next pair's hop over this pair's LDS reads (1.65 ms) and
+// 512-thread workgroups (1.71 ms) gain nothing.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -32,7 +41,7 @@ namespace lqcd {
 
 namespace {
 
-constexpr int kForceBlock = 256;  // 64 odd sites x 4 directions
+constexpr int kForceBlock = 256;  // 4 directions x 64 odd sites
 constexpr int kActionBlock = 256;
 constexpr int kCombineBlock = 256;
 
@@ -53,51 +62,34 @@ constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
 double* g_scratch_dev[kMaxScratchDevices] = {};
 
-// The value of lane (l ^ 1) (CTRL 0xB1: quad permutation 1,0,3,2) or of lane
-// (l ^ 2) (CTRL 0x4E: 2,3,0,1) of the same quad, moved by DPP in the vector
-// pipeline (no LDS round trip).
-template <int CTRL>
-__device__ __forceinline__ double dpp_quad(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
-  return __hiloint2double(hi, lo);
-}
-
-// Sum over the four lanes of a quad: v + v[l ^ 1], then + the partner pair's
-// sum; every lane of the quad ends with the same bits.
-__device__ __forceinline__ double quad_sum(double v) {
-  v += dpp_quad<0xB1>(v);
-  v += dpp_quad<0x4E>(v);
-  return v;
-}
-
-__global__ void __launch_bounds__(kForceBlock) k_force(const KGeom g,
-                                                       const double2* __restrict__ U,
-                                                       const double2* __restrict__ X, int npf,
-                                                       int nshift, const Alphas al, int mode,
-                                                       int accumulate, int ty, int tz,
-                                                       double2* __restrict__ F) {
+__global__ void __launch_bounds__(kForceBlock, 2) k_force(const KGeom g,
+                                                          const double2* __restrict__ U,
+                                                          const double2* __restrict__ X, int npf,
+                                                          int nshift, const Alphas al, int mode,
+                                                          int accumulate, int ty, int tz,
+                                                          double2* __restrict__ F) {
   // Every even X is read by its eight odd neighbours, for every pair, so the
   // sites sharing neighbours run close together and on one XCD (one L2):
   // consecutive blocks of an XCD take consecutive sites of a (y, z)-tiled
-  // order with t inside the tile.
-  const int lb = xcd_block(blockIdx.x, gridDim.x, 1);
-  const int64_t tid = int64_t(lb) * blockDim.x + threadIdx.x;
-  const int i = int(tid >> 2);
-  const int mu = int(tid & 3);
-  if (i >= g.Vh) return;  // whole quads leave together
-  const int h = tiled_half_index(g, i, ty, tz);  // odd site
+  // order with t inside the tile, and the four waves of a workgroup, in step
+  // over the pairs, find most of a site's neighbours in L1.
+  __shared__ double2 part[2][4][3][64];
+  const int lane = threadIdx.x & 63;
+  const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i0 = xcd_block(blockIdx.x, gridDim.x, 1) * 64 + lane;
+  const bool in = i0 < g.Vh;  // lanes past Vh work on the first site and store nothing
+  const int h = tiled_half_index(g, in ? i0 : 0, ty, tz);  // odd site
   const Site s = decode_site(g, h, 1);
   int fwd[4], bwd[4];
   neighbours(g, s, h, fwd, bwd);
-  double eta[4];
-  staggered_eta(s, eta);
-  double sf = eta[mu], sb = eta[mu];  // eta_mu(y) s_mu(y), eta_mu(y-mu) s_mu(y-mu)
+  const int hf = mu == 0 ? fwd[0] : mu == 1 ? fwd[1] : mu == 2 ? fwd[2] : fwd[3];
+  const int hb = mu == 0 ? bwd[0] : mu == 1 ? bwd[1] : mu == 2 ? bwd[2] : bwd[3];
+  const int ep = ((mu >= 1 ? s.x : 0) + (mu >= 2 ? s.y : 0) + (mu >= 3 ? s.z : 0)) & 1;
+  double sf = ep ? -1.0 : 1.0, sb = sf;  // eta_mu(y) s_mu(y), eta_mu(y-mu) s_mu(y-mu)
   if (mu == 3 && g.anti) {
     if (s.t == g.Lt - 1) sf = -sf;
     if (s.t == 0) sb = -sb;
   }
-  const int hf = fwd[mu], hb = bwd[mu];
   const int64_t pstride = int64_t(4) * 9 * g.Vh;
   Su3<double> Uf, Ub;
   load_link<double, 9>(U + pstride + int64_t(mu) * 9 * g.Vh, h, g.Vh, Uf);  // (y, mu), y odd
@@ -115,45 +107,65 @@ __global__ void __launch_bounds__(kForceBlock) k_force(const KGeom g,
   }
 
   const int64_t vs = int64_t(3) * g.Vh;
-  for (int j = 0; j < npf; ++j) {
-    for (int i = 0; i < nshift; ++i) {
-      const double2* Xk = X + (int64_t(j) * nshift + i) * vs;
-      cplx<double> xf[3], xb[3], y1[3], y2[3], chi[3];
+  const int npair = npf * nshift;
+  cplx<double> xf[3], xb[3];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        xf[c] = Xk[int64_t(c) * g.Vh + hf];
-        xb[c] = Xk[int64_t(c) * g.Vh + hb];
-      }
-      // direction-mu part of chi(y) = 1/2 [sf U_mu(y) X(y+mu) - sb U_mu(y-mu)^dag X(y-mu)]
-      mat_vec<double>(Uf, xf, y1);
-      adj_mat_vec<double>(Ub, xb, y2);
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        chi[c].x = quad_sum(y1[c].x - y2[c].x);
-        chi[c].y = quad_sum(y1[c].y - y2[c].y);
-      }
-      // chi already carries the 1/2 of D_oe; the 1/2 of dD_oe and the factor 2 of
-      // the variation cancel, so M takes alpha * eta * s with no further factor:
-      //   M_mu(y)    += cf X(y+mu) chi(y)^dag,   cf = -alpha sf
-      //   M_mu(y-mu) += cb chi(y) X(y-mu)^dag,   cb =  alpha sb
-      // with the coefficients folded into chi once per pair.
-      const double cf = -al.a[i] * sf;
-      const double cb = al.a[i] * sb;
-      cplx<double> cfc[3], cbc[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        cfc[c] = mk<double>(cf * chi[c].x, -cf * chi[c].y);  // cf conj(chi)
-        cbc[c] = cscale<double>(cb, chi[c]);
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-          cfma<double>(Mf.e[3 * a + b], xf[a], cfc[b]);
-          cfmac<double>(Mb.e[3 * a + b], xb[b], cbc[a]);  // += cb chi[a] conj(xb[b])
-        }
-    }
+  for (int c = 0; c < 3; ++c) {
+    xf[c] = X[int64_t(c) * g.Vh + hf];
+    xb[c] = X[int64_t(c) * g.Vh + hb];
   }
+  int i = 0;  // shift of the pair
+#pragma unroll 1
+  for (int k = 0; k < npair; ++k) {
+    cplx<double> y1[3], y2[3], chi[3], cfc[3], cbc[3];
+    // direction-mu part of chi(y) = 1/2 [sf U_mu(y) X(y+mu) - sb U_mu(y-mu)^dag X(y-mu)]
+    mat_vec<double>(Uf, xf, y1);
+    adj_mat_vec<double>(Ub, xb, y2);
+    double2 (&pk)[4][3][64] = part[k & 1];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) pk[mu][c][lane] = csub<double>(y1[c], y2[c]);
+    // the next pair's loads, in flight over the barrier and the outer products
+    const double2* Xn = X + int64_t(k + 1 < npair ? k + 1 : k) * vs;
+    cplx<double> nf[3], nb[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      nf[c] = Xn[int64_t(c) * g.Vh + hf];
+      nb[c] = Xn[int64_t(c) * g.Vh + hb];
+    }
+    // One barrier per pair: a wave writes a buffer again two pairs later, after a
+    // barrier that every wave reaches only when it has read this one.
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      chi[c] = cadd<double>(cadd<double>(pk[0][c][lane], pk[1][c][lane]),
+                            cadd<double>(pk[2][c][lane], pk[3][c][lane]));
+    // chi already carries the 1/2 of D_oe; the 1/2 of dD_oe and the factor 2 of
+    // the variation cancel, so M takes alpha * eta * s with no further factor:
+    //   M_mu(y)    += cf X(y+mu) chi(y)^dag,   cf = -alpha sf
+    //   M_mu(y-mu) += cb chi(y) X(y-mu)^dag,   cb =  alpha sb
+    // with the coefficients folded into chi once per pair.
+    const double cf = -al.a[i] * sf;
+    const double cb = al.a[i] * sb;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      cfc[c] = mk<double>(cf * chi[c].x, -cf * chi[c].y);  // cf conj(chi)
+      cbc[c] = cscale<double>(cb, chi[c]);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+      for (int b = 0; b < 3; ++b) {
+        cfma<double>(Mf.e[3 * a + b], xf[a], cfc[b]);
+        cfmac<double>(Mb.e[3 * a + b], xb[b], cbc[a]);  // += cb chi[a] conj(xb[b])
+      }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      xf[c] = nf[c];
+      xb[c] = nb[c];
+    }
+    i = i + 1 == nshift ? 0 : i + 1;
+  }
+  if (!in) return;
   // the unscaled links for the projection: U = (2 s) U', exactly
 #pragma unroll
   for (int e = 0; e < 9; ++e) {
@@ -354,9 +366,8 @@ int lqcd_fermion_force(const lqcd_geom* g, const void* U64, int32_t npf, int32_t
   for (int i = 0; i < nshift; ++i) al.a[i] = alpha[i];
   const int64_t threads = int64_t(4) * k.Vh;
   const unsigned grid = unsigned((threads + kForceBlock - 1) / kForceBlock);
-  // small (y, z) tiles: a tile's t slice is a few dozen waves, so the +-t
-  // neighbours of a site are loaded by waves at nearly the same pair (at 48^4
-  // 6 x 6 tiles: 11.4 ms against 12.4 ms lexicographic, both XCD-contiguous)
+  // small (y, z) tiles keep a site's +-z and +-t neighbours near in launch order:
+  // at 48^4 4 x 4 to 12 x 6 tiles are within 3 %, 2 x 2 tiles 7 % slower
   const int tz = small_tile(k.Lz), ty = small_tile(k.Ly) ? small_tile(k.Ly) : k.Ly;
   hipLaunchKernelGGL(k_force, dim3(grid), dim3(kForceBlock), 0, (hipStream_t)stream, k,
                      (const double2*)U64, (const double2*)X, npf, nshift, al, mode, accumulate,
