@@ -178,18 +178,30 @@ def _check(status: int, allow=()):
     return status
 
 
-def _stream():
-    return _vp(torch.cuda.current_stream().cuda_stream)
+# Small lattices are bound by the time that a call takes on the host (8^4 hop:
+# 7.4 us, of which the launch 4.4; 11.8 with a torch.cuda.Stream object, which
+# takes 3 us to build, and every format looked up twice).  So the pointers and
+# the stream are passed as plain integers, and the stream comes from the raw
+# query where this torch has it.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
-def _ptr(t: torch.Tensor | None):
+def _stream() -> int:
+    """The current stream of the current device."""
+    if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
+
+
+def _ptr(t: torch.Tensor | None) -> int:
     if t is None:
-        return _vp(0)
+        return 0
     if not t.is_cuda:
         raise ValueError("tensor must live on the GPU")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return _vp(t.data_ptr())
+    return t.data_ptr()
 
 
 @dataclass(frozen=True)
@@ -203,7 +215,8 @@ class Geometry:
 
     @property
     def Vh(self) -> int:
-        return self.V // 2
+        L = self.L
+        return L[0] * L[1] * L[2] * L[3] // 2
 
     def c(self):
         g = lqcd_geom()
@@ -308,12 +321,8 @@ def unpack_spinor(geom: Geometry, packed: torch.Tensor, parity: int, out=None):
     return out
 
 
-def _prec_of(t):
-    return F64 if t.dtype == torch.complex128 else F32
-
-
-def _fmt_of(U):
-    return {9: LINKS18, 6: LINKS12, 7: LINKS12D, 13: LINKS12T}[int(U.shape[2])]
+_PRECS = {torch.complex128: F64, torch.complex64: F32}
+_FMTS = {9: LINKS18, 6: LINKS12, 7: LINKS12D, 13: LINKS12T}  # by the elements of a link
 
 
 # ---------------------------------------------------------------- argument checks
@@ -345,13 +354,14 @@ def _gpu(*ts):
 def _links_arg(geom: Geometry, U, name="U", prec=None, fmt=None):
     """Packed links [2][4][NE][Vh]; returns (prec, fmt)."""
     _tensor(U, name)
-    if U.dtype not in (torch.complex128, torch.complex64):
+    p = _PRECS.get(U.dtype)
+    if p is None:
         raise ValueError(f"{name} must be complex128 or complex64 packed links, got {U.dtype}")
-    if U.dim() != 4 or tuple(U.shape[:2]) != (2, 4) or int(U.shape[2]) not in (9, 6, 7, 13) \
-            or int(U.shape[3]) != (geom.Vh // 2 if int(U.shape[2]) == 13 else geom.Vh):
+    s = U.shape
+    f = _FMTS.get(s[2]) if len(s) == 4 and s[0] == 2 and s[1] == 4 else None
+    if f is None or s[3] != (geom.Vh // 2 if f == LINKS12T else geom.Vh):
         raise ValueError(f"{name} must be packed links [2][4][9|6|7][{geom.Vh}] or "
                          f"[2][4][13][{geom.Vh // 2}], got {tuple(U.shape)}")
-    p, f = _prec_of(U), _fmt_of(U)
     if prec is not None and p != prec:
         raise ValueError(f"{name} must be {_cdtype(prec)}, got {U.dtype}")
     if fmt is not None and f != fmt:
@@ -370,14 +380,15 @@ def _spinor_arg(geom: Geometry, t, prec, name, n=None):
     if t.dtype != _cdtype(prec):
         raise ValueError(f"{name} must be {_cdtype(prec)} to match the links, got {t.dtype}")
     per = 3 * geom.Vh
-    if t.numel() == 0 or t.numel() % per:
+    m = t.numel()
+    if m == 0 or m % per:
         raise ValueError(f"{name} must hold a whole number of packed spinors of 3 x {geom.Vh} "
-                         f"entries, got {t.numel()} entries")
-    if n is not None and t.numel() != n * per:
+                         f"entries, got {m} entries")
+    if n is not None and m != n * per:
         raise ValueError(f"{name} must hold {n} packed spinors ({n * per} entries), "
-                         f"got {t.numel()}")
+                         f"got {m}")
     _finish(t, name)
-    return t.numel() // per
+    return m // per
 
 
 def _real_links_out(geom: Geometry, t, name):
@@ -385,38 +396,36 @@ def _real_links_out(geom: Geometry, t, name):
     _links_arg(geom, t, name, F64, LINKS18)
 
 
+def _hop(entry, geom, U, x, name, out):
+    prec, fmt = _links_arg(geom, U)
+    n = _spinor_arg(geom, x, prec, name)
+    if out is None:
+        out = torch.empty_like(x)
+    _spinor_arg(geom, out, prec, "out", n)
+    _check(_fn(entry)(geom.c(), prec, fmt, _ptr(U), _ptr(x), _ptr(out), n, _stream()))
+    return out
+
+
 def doe(geom: Geometry, U, psi_even, out=None):
     """D_oe: packed even spinors [n][3][Vh] -> packed odd spinors."""
-    prec, _ = _links_arg(geom, U)
-    n = _spinor_arg(geom, psi_even, prec, "psi_even")
-    out = torch.empty_like(psi_even) if out is None else out
-    _spinor_arg(geom, out, prec, "out", n)
-    _check(_fn("lqcd_doe")(geom.c(), _prec_of(U), _fmt_of(U), _ptr(U), _ptr(psi_even),
-                           _ptr(out), n, _stream()))
-    return out
+    return _hop("lqcd_doe", geom, U, psi_even, "psi_even", out)
 
 
 def deo(geom: Geometry, U, psi_odd, out=None):
     """D_eo: packed odd spinors -> packed even spinors."""
-    prec, _ = _links_arg(geom, U)
-    n = _spinor_arg(geom, psi_odd, prec, "psi_odd")
-    out = torch.empty_like(psi_odd) if out is None else out
-    _spinor_arg(geom, out, prec, "out", n)
-    _check(_fn("lqcd_deo")(geom.c(), _prec_of(U), _fmt_of(U), _ptr(U), _ptr(psi_odd),
-                           _ptr(out), n, _stream()))
-    return out
+    return _hop("lqcd_deo", geom, U, psi_odd, "psi_odd", out)
 
 
 def apply_A(geom: Geometry, U, mass, sigma, x_even, out=None, tmp=None):
     """((m^2 + sigma) - D_eo D_oe) x on packed even spinors."""
-    prec, _ = _links_arg(geom, U)
+    prec, fmt = _links_arg(geom, U)
     n = _spinor_arg(geom, x_even, prec, "x_even")
     out = torch.empty_like(x_even) if out is None else out
     tmp = torch.empty_like(x_even) if tmp is None else tmp
     _spinor_arg(geom, out, prec, "out", n)
     _spinor_arg(geom, tmp, prec, "tmp", n)
-    _check(_fn("lqcd_apply_A")(geom.c(), _prec_of(U), _fmt_of(U), _ptr(U), float(mass),
-                               float(sigma), _ptr(x_even), _ptr(out), _ptr(tmp), n, _stream()))
+    _check(_fn("lqcd_apply_A")(geom.c(), prec, fmt, _ptr(U), float(mass), float(sigma),
+                               _ptr(x_even), _ptr(out), _ptr(tmp), n, _stream()))
     return out
 
 
