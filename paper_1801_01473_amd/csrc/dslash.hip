@@ -108,6 +108,13 @@ constexpr int kTuneCacheFormat = 1;
 // Half volumes up to which the direction-split stencil is a candidate.
 constexpr int kSplitMaxVh = 1 << 18;
 
+// Half volumes up to which the plain modes try it with one right-hand side per
+// pass over the links although there are several.  The timings below repeat on
+// one link field, which larger lattices' callers may have moved out of the
+// 256 MB cache in between: 18 x 22 x 20 x 26, FP64, 3 right-hand sides, A x:
+// 55 us on one field but 74 on three in turn, against 57 and 67 in pairs.
+constexpr int kSplitOncePerRhsVh = 1 << 16;
+
 // What the split kernel saves elsewhere when it can take over the step length
 // (up to kFusedPartials partials): the one-workgroup kernels of the scalars, 5
 // and 4 us a launch at 16^4, against about 1 us more in the CG kernels each.
@@ -282,6 +289,8 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     for (int b : {1, 2}) {
       if (forced ? b != forced : b > c.nrhs) continue;
       if (c.pairs && b == 1) continue;
+      if (b == 1 && c.nrhs > 1 && !forced && c.mode != DM_CG && c.g.Vh > kSplitOncePerRhsVh)
+        continue;
       for (int x : {0, 1}) {
         DslashCfg v;
         v.block = 256;
