@@ -26,9 +26,11 @@
 // 2 launches instead of 12.  Both passes are bound by their memory path, not
 // by arithmetic (with the products taken out of a copy they took the same
 // time): pass 1 by HBM (3.1 GB of links read ~3 times through 4 MB L2s, 6.1 GB
-// written, 3.8 ms at 48^4), pass 2 by the L2-to-L1 traffic, about 12 TB/s, so
-// the links that the waves of a workgroup share go through LDS (4.5 -> 3.7 ms).
-// 48^4: 25.6 ms with stored staples, 7.4 ms now; 32^3 x 48: 2.1 ms.
+// written, 3.6 ms at 48^4), pass 2 by what misses L2 (60 % of its requests, 25 GB
+// at 6.5 TB/s: the sites in flight on an XCD have 9 MB of fields, links and
+// forces), so the links that the waves of a workgroup share go through LDS
+// (4.5 -> 3.7 ms).
+// 48^4: 25.6 ms with stored staples, 7.2 ms now.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -149,17 +151,18 @@ __device__ __forceinline__ PlaneSite plane_site(const KGeom& g, const double2* _
   return p;
 }
 
-// One workgroup per 64 half indices of one parity, wave = plane.
-__global__ void __launch_bounds__(384, 3) k_loops(KGeom g, const double2* __restrict__ U,
+// One workgroup per 64 half indices of both parities, wave = plane.
+__global__ void __launch_bounds__(768, 3) k_loops(KGeom g, const double2* __restrict__ U,
                                                   const Planes pl, double w0, double w1, int ty,
                                                   int tz, double2* __restrict__ P) {
-  __shared__ Ahead sh;
-  const ChunkSite cs = chunk_site(g, ty, tz);
+  __shared__ Ahead ahead[2];
+  const ChunkSite cs = chunk_pair_site(g, pl.n, ty, tz);
+  Ahead& sh = ahead[cs.par];
   const int lane = cs.lane, task = cs.task, a = pl.a[task], b = pl.b[task];
   const PlaneSite p = plane_site(g, U, cs, pl.n, a, b, sh);
   if (!cs.in) return;
   // (the barriers keep the compiler from loading every section's links at
-  // once: 168 registers without spilling, so two workgroups share a CU)
+  // once: 168 registers without spilling, three waves a SIMD)
   const M3 c1 = lds_mul(sh[0][a], lane, ld_m3(p.b_o, p.a1, g.Vh));  // a, b
   __builtin_amdgcn_sched_barrier(0);
   const M3 c2 = lds_mul(sh[0][b], lane, ld_m3(p.a_o, p.b1, g.Vh));  // b, a
@@ -196,16 +199,18 @@ __device__ __forceinline__ double re_tr_dag(const M3& a, const M3& b) {
 
 // The action of the loops whose first corner is x, one plane per wave as in
 // k_loops: w (1 - Re Tr / 3) of the plaquette and of both rectangles, 8 products
-// per plane (the last one of each loop is only a trace).  24^3 x 48: 0.38 ms, bound
-// by 44 link matrices per site from L2 (4.2 GB at 11 TB/s); one thread per site
-// over all loops, 13 products per plane, took 1.03 ms.
-__global__ void __launch_bounds__(384, 3) k_loop_action(KGeom g, const double2* __restrict__ U,
+// per plane (the last one of each loop is only a trace).  24^3 x 48: 0.30 ms, bound
+// by the latency of 44 link matrices per site, 4.2 GB, of which L2 holds 86 %
+// (14 TB/s at 12 waves a CU; one parity a workgroup, 6 waves a CU, 0.38 ms); one
+// thread per site over all loops, 13 products per plane, took 1.03 ms.
+__global__ void __launch_bounds__(768, 3) k_loop_action(KGeom g, const double2* __restrict__ U,
                                                         const Planes pl, double c0, double c1,
                                                         int ty, int tz,
                                                         double* __restrict__ part) {
-  __shared__ Ahead sh;
-  __shared__ double lds[6];
-  const ChunkSite cs = chunk_site(g, ty, tz);
+  __shared__ Ahead ahead[2];
+  __shared__ double lds[12];
+  const ChunkSite cs = chunk_pair_site(g, pl.n, ty, tz);
+  Ahead& sh = ahead[cs.par];
   const int lane = cs.lane, a = pl.a[cs.task], b = pl.b[cs.task];
   const PlaneSite p = plane_site(g, U, cs, pl.n, a, b, sh);
   const M3 ca = lds_mul(sh[0][a], lane, ld_m3(p.b_o, p.a1, g.Vh));  // a, b
@@ -315,13 +320,13 @@ Planes plane_pass(int lo, int hi, int accumulate, int* seen) {
 
 }  // namespace
 
-unsigned gauge_action_blocks(const KGeom& k) { return chunk_blocks(k.Vh); }
+unsigned gauge_action_blocks(const KGeom& k) { return chunk_pair_blocks(k.Vh); }
 
 int gauge_action_partials(const KGeom& k, const double2* U, double c1, double* part,
                           hipStream_t s) {
   int seen = 0;
   const Planes p = plane_pass(0, 6, 0, &seen);
-  hipLaunchKernelGGL(k_loop_action, dim3(gauge_action_blocks(k)), dim3(64 * p.n), 0, s, k, U, p,
+  hipLaunchKernelGGL(k_loop_action, dim3(gauge_action_blocks(k)), dim3(128 * p.n), 0, s, k, U, p,
                      1.0 - 8.0 * c1, c1, chunk_tile(k.Ly, 16), chunk_tile(k.Lz, 7), part);
   LQCD_LAUNCH_CHECK();
   return LQCD_OK;
@@ -379,7 +384,7 @@ int lqcd_gauge_force_staples(const lqcd_geom* g, const void* U64, double beta, d
   for (int lo = 0; lo < 6; lo += step) {
     Planes p = plane_pass(lo, lo + step, accumulate, &seen);
     p.sh = chunk_shift(k.Vh);
-    hipLaunchKernelGGL(k_loops, dim3(chunk_blocks(k.Vh)), dim3(64 * p.n), 0, s, k, U, p, w0, w1,
+    hipLaunchKernelGGL(k_loops, dim3(chunk_pair_blocks(k.Vh)), dim3(128 * p.n), 0, s, k, U, p, w0, w1,
                        ty, tz, P);
     LQCD_LAUNCH_CHECK();
     hipLaunchKernelGGL(k_loop_force, dim3(chunk_blocks(k.Vh)), dim3(256), 0, s, k, U, P, p, w1,

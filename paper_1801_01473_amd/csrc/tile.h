@@ -125,6 +125,24 @@ __device__ __forceinline__ ChunkSite chunk_site(const KGeom& g, int ty, int tz) 
   return c;
 }
 
+// The same with both parities of the 64 entries in one workgroup, its first
+// ntask waves taking parity 0: for six tasks, whose 6 waves do not spread evenly
+// over the 4 SIMDs of a CU, so that of two such workgroups that would fit by
+// registers and LDS only one is ever resident (5.6 waves a CU measured).
+inline unsigned chunk_pair_blocks(int Vh) { return unsigned((Vh + 63) / 64); }
+
+__device__ __forceinline__ ChunkSite chunk_pair_site(const KGeom& g, int ntask, int ty, int tz) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  ChunkSite c;
+  c.par = w >= ntask;
+  c.lane = threadIdx.x & 63;
+  c.task = w - c.par * ntask;
+  const int i = xcd_block(blockIdx.x, gridDim.x, 1) * 64 + c.lane;
+  c.in = i < g.Vh;
+  c.h = tiled_half_index(g, c.in ? i : 0, ty, tz);
+  return c;
+}
+
 // Tile edges for those kernels: the largest divisor of Ly up to 16 and of Lz
 // up to 7.  Their sites in flight and the +-2 neighbourhood compete for 4 MB of
 // L2: at 48^4 the gauge force takes 7.4 ms with 8 x 6 to 16 x 6 tiles, 7.7 ms
