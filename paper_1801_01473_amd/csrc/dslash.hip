@@ -116,7 +116,7 @@ constexpr int kSplitMaxVh = 1 << 18;
 constexpr int kSplitOncePerRhsVh = 1 << 16;
 
 // What the split kernel saves elsewhere when it can take over the step length
-// (up to kFusedPartials partials): the one-workgroup kernels of the scalars, 5
+// (fused_partials_pay): the one-workgroup kernels of the scalars, 5
 // and 4 us a launch at 16^4, against about 1 us more in the CG kernels each.
 // Its times in CG mode are ranked with this credit.
 constexpr float kFusedCreditMs = 0.006f;
@@ -367,7 +367,7 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     return LQCD_OK;
   };
 
-  const bool fusable = cg && (c.g.Vh + 63) / 64 <= kFusedPartials;
+  const bool fusable = cg && fused_partials_pay((c.g.Vh + 63) / 64, c.nrhs);
   auto ranked = [&](float ms, const DslashCfg& cfg) {
     return fusable && cfg.sp == 1 ? ms - kFusedCreditMs : ms;
   };

@@ -1395,8 +1395,9 @@ int read_flags(const Ctx& c, GlobalFlags* host) {
 // sum, and only the base direction may need a new coefficient in the update.
 bool fused_scalars(const Ctx& c, const Core& k, const Phase& ph) {
   const int nbv = (c.g.Vh + kVecBlock - 1) / kVecBlock;
-  return ph.c_eo.sp == 1 && fused_scalars_enabled() && (k.win > 1 || k.nshift == 1) && ph.nb_oe <= kFusedPartials &&
-         ph.nb_eo <= kFusedPartials && nbv <= kFusedPartials;
+  const int nb = std::max({ph.nb_oe, ph.nb_eo, nbv});
+  return ph.c_eo.sp == 1 && fused_scalars_enabled() && (k.win > 1 || k.nshift == 1) &&
+         fused_partials_pay(nb, k.nsys);
 }
 
 int tune_phase(const Ctx& c, const Core& k, Phase& ph) {

@@ -7,10 +7,21 @@
 
 namespace lqcd {
 
-// Partial counts up to this fit the one-pass reduction below.
-constexpr int kFusedPartials = kScalarThreads;
+// Partial counts up to this can go through the reduction below in every
+// workgroup of a kernel, instead of a kernel of one workgroup.
+constexpr int kFusedPartials = 2 * kScalarThreads;
 
-// The sums of K arrays of n[k] <= kScalarThreads doubles by a workgroup of 256
+// Whether that pays: nb workgroups a right-hand side then read nb partials each
+// from L2, nb^2 nrhs doubles in all and twice that for the step length.  CG and
+// mixed multi-shift, ms, without and with: 20^4 (nb 1250) 13.6 and 12.3, with two
+// right-hand sides 15.2 and 14.2; 22^3 x 24 (1997) 17.7 and 15.9; but 24 x 20^2 x
+// 26 (1950) with two 18.3 and 19.7, 16^3 x 30 (960) with four 16.1 and 17.9, 16^4
+// (512) with eight 15.4 and 16.8, with four 12.3 and 12.1.
+inline bool fused_partials_pay(int64_t nb, int nrhs) {
+  return nb <= kFusedPartials && nb * nb * nrhs <= (int64_t(1) << (nrhs <= 2 ? 22 : 20));
+}
+
+// The sums of K arrays of n[k] <= kFusedPartials doubles by a workgroup of 256
 // threads, in the order in which a workgroup of kScalarThreads threads (wg_sum)
 // adds them -- 16 groups of 64, a butterfly in each, the groups in order -- so
 // with the same bits.  All loads are issued before the first butterfly.  Every
@@ -30,6 +41,15 @@ struct SmallSums {
         const int i = (int(threadIdx.x >> 6) + NW * m) * 64 + int(threadIdx.x & 63);
         v[k][m] = i < n[k] ? p[k][i] : 0.0;
       }
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (n[k] > kScalarThreads)
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+          const int i = kScalarThreads + (int(threadIdx.x >> 6) + NW * m) * 64 +
+                        int(threadIdx.x & 63);
+          v[k][m] += i < n[k] ? p[k][i] : 0.0;
+        }
   }
   // sums groups of 64 into LDS; a barrier goes between this and sum()
   __device__ __forceinline__ void reduce(double (&lds)[K][W]) {
