@@ -366,7 +366,8 @@ def rhmc_trajectory_bench(lq, torch, g48, U48):
     (dH(20) / dH(40) ~ 4 for the second-order scheme) and the multi-step
     scheme (10 outer fermion steps, 4 gauge substeps each): time, dH and the
     accept decision.  Then the tree-level Symanzik gauge force kernel alone on
-    the workload lattice: 85 SU(3) products (198 flops each) per link, against
+    the workload lattice: 85 SU(3) products (198 flops each) per link when every
+    staple is multiplied out (the loop form executes about 29), against
     the FP64 vector peak."""
     import synth
     L = (16, 16, 16, 16)

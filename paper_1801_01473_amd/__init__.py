@@ -699,7 +699,7 @@ def gauge_action(geom: Geometry, U64, beta: float, c1: float = SYMANZIK_C1) -> f
 def gauge_force(geom: Geometry, U64, beta: float, c1: float = SYMANZIK_C1, out=None,
                 accumulate=False, method: str = "staples"):
     """F = TA(U M) of S_g, packed like the links; accumulate adds into out.
-    method "staples": through stored plaquette-staple fields (workspace);
+    method "staples": through the stored loops of each plane (workspace);
     "direct": every staple of every link multiplied out in place."""
     _u64_arg(geom, U64)
     out = empty_links(geom, F64, LINKS18, U64.device) if out is None else out
