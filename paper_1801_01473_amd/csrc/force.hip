@@ -19,14 +19,15 @@
 // At the end the lane projects U M to the traceless anti-Hermitian part (mode 0)
 // or writes M^dag (mode 1, torch's gradient).
 //
-// At 32^3 x 48 with 48 pairs the kernel takes 1.62 ms (1.74 ms with four lanes
+// At 32^3 x 48 with 48 pairs the kernel takes 1.63 ms (1.74 ms with four lanes
 // of one wave per site and two shuffles per pair): 464 M vector instructions
-// keep the FP64 units busy 55-65 % of the time at the 1.9-2.0 GHz that the card
+// keep the FP64 units busy 55 % of the time at the 1.9-2.0 GHz that the card
 // holds under them, 15 GB of loads go through L1 (11 GB from L2, 4.9 GB from
 // memory against 2.7 GB that must be read).  With every X read from L2 it would
-// take 1.42 ms.  Two lanes per link at twice the waves (1.67 ms), loads two pairs
-// ahead (1.62 ms), the next pair's hop over this pair's LDS reads (1.65 ms) and
-// 512-thread workgroups (1.71 ms) gain nothing.
+// take 1.42 ms.  Two lanes per link at twice the waves (1.67 ms), loads one pair
+// ahead (1.63 ms, but 3 % slower where few waves are in flight), the next pair's
+// hop over this pair's LDS reads (1.65 ms) and two sites' waves in a workgroup
+// (1.71 ms) gain nothing.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -42,6 +43,12 @@ namespace lqcd {
 namespace {
 
 constexpr int kForceBlock = 256;  // 4 directions x 64 odd sites
+
+// Up to 256 workgroups, one a CU, a workgroup has two groups of four waves that
+// take every other pair: a wave is then bound by the latency of one pair after
+// the other, 0.7 us.  4 x 12 pairs: 8^4 30 us (40 with one group), 12^4 34 us (42);
+// past one workgroup a CU it loses, 16^4 78 us (74), with 4 pairs 26 us (18).
+constexpr int kForceGroupsVh = 64 * 256;
 constexpr int kActionBlock = 256;
 constexpr int kCombineBlock = 256;
 
@@ -62,7 +69,8 @@ constexpr int kMaxScratchDevices = 64;
 std::mutex g_scratch_mu;
 double* g_scratch_dev[kMaxScratchDevices] = {};
 
-__global__ void __launch_bounds__(kForceBlock, 2) k_force(const KGeom g,
+template <int G>
+__global__ void __launch_bounds__(G * kForceBlock, 2) k_force(const KGeom g,
                                                           const double2* __restrict__ U,
                                                           const double2* __restrict__ X, int npf,
                                                           int nshift, const Alphas al, int mode,
@@ -71,11 +79,13 @@ __global__ void __launch_bounds__(kForceBlock, 2) k_force(const KGeom g,
   // Every even X is read by its eight odd neighbours, for every pair, so the
   // sites sharing neighbours run close together and on one XCD (one L2):
   // consecutive blocks of an XCD take consecutive sites of a (y, z)-tiled
-  // order with t inside the tile, and the four waves of a workgroup, in step
+  // order with t inside the tile, and the waves of a workgroup, in step
   // over the pairs, find most of a site's neighbours in L1.
-  __shared__ double2 part[2][4][3][64];
+  __shared__ double2 parts[G][2][4][3][64];
   const int lane = threadIdx.x & 63;
-  const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int mu = w & 3, grp = w >> 2;
+  double2 (&part)[2][4][3][64] = parts[grp];
   const int i0 = xcd_block(blockIdx.x, gridDim.x, 1) * 64 + lane;
   const bool in = i0 < g.Vh;  // lanes past Vh work on the first site and store nothing
   const int h = tiled_half_index(g, in ? i0 : 0, ty, tz);  // odd site
@@ -85,7 +95,7 @@ __global__ void __launch_bounds__(kForceBlock, 2) k_force(const KGeom g,
   const int hf = mu == 0 ? fwd[0] : mu == 1 ? fwd[1] : mu == 2 ? fwd[2] : fwd[3];
   const int hb = mu == 0 ? bwd[0] : mu == 1 ? bwd[1] : mu == 2 ? bwd[2] : bwd[3];
   const int ep = ((mu >= 1 ? s.x : 0) + (mu >= 2 ? s.y : 0) + (mu >= 3 ? s.z : 0)) & 1;
-  double sf = ep ? -1.0 : 1.0, sb = sf;  // eta_mu(y) s_mu(y), eta_mu(y-mu) s_mu(y-mu)
+  double sf = ep ? -1.0 : 1.0, sb = -sf;  // eta_mu(y) s_mu(y), -eta_mu(y-mu) s_mu(y-mu)
   if (mu == 3 && g.anti) {
     if (s.t == g.Lt - 1) sf = -sf;
     if (s.t == 0) sb = -sb;
@@ -106,75 +116,100 @@ __global__ void __launch_bounds__(kForceBlock, 2) k_force(const KGeom g,
     Ub.e[e] = cscale<double>(0.5 * sb, Ub.e[e]);
   }
 
-  const int64_t vs = int64_t(3) * g.Vh;
   const int npair = npf * nshift;
-  cplx<double> xf[3], xb[3];
+  const uint32_t of = uint32_t(hf) * uint32_t(sizeof(double2));
+  const uint32_t ob = uint32_t(hb) * uint32_t(sizeof(double2));
+  const int64_t cs = int64_t(g.Vh) * sizeof(double2);
+  const char* p = reinterpret_cast<const char*>(X) + 3 * cs * grp;
+  auto load_x = [&](cplx<double>* vf, cplx<double>* vb) {
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    xf[c] = X[int64_t(c) * g.Vh + hf];
-    xb[c] = X[int64_t(c) * g.Vh + hb];
-  }
-  int i = 0;  // shift of the pair
-#pragma unroll 1
-  for (int k = 0; k < npair; ++k) {
-    cplx<double> y1[3], y2[3], chi[3], cfc[3], cbc[3];
-    // direction-mu part of chi(y) = 1/2 [sf U_mu(y) X(y+mu) - sb U_mu(y-mu)^dag X(y-mu)]
+    for (int c = 0; c < 3; ++c) {
+      vf[c] = *reinterpret_cast<const double2*>(p + c * cs + of);
+      vb[c] = *reinterpret_cast<const double2*>(p + c * cs + ob);
+    }
+  };
+  // step of the loop, this group's pair and its shift
+  int j = 0, k = grp, i = G > 1 && grp >= nshift ? 0 : grp;
+  const int steps = (npair + G - 1) / G;
+  auto pair = [&](const cplx<double>* xf, const cplx<double>* xb, cplx<double>* nf,
+                  cplx<double>* nb, double2 (&pk)[4][3][64]) {
+    // direction-mu part of chi(y) = 1/2 [sf U_mu(y) X(y+mu) + sb U_mu(y-mu)^dag X(y-mu)]
+    cplx<double> y1[3], y2[3];
     mat_vec<double>(Uf, xf, y1);
     adj_mat_vec<double>(Ub, xb, y2);
-    double2 (&pk)[4][3][64] = part[k & 1];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) pk[mu][c][lane] = csub<double>(y1[c], y2[c]);
-    // the next pair's loads, in flight over the barrier and the outer products
-    const double2* Xn = X + int64_t(k + 1 < npair ? k + 1 : k) * vs;
-    cplx<double> nf[3], nb[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      nf[c] = Xn[int64_t(c) * g.Vh + hf];
-      nb[c] = Xn[int64_t(c) * g.Vh + hb];
-    }
-    // One barrier per pair: a wave writes a buffer again two pairs later, after a
+    for (int c = 0; c < 3; ++c) pk[mu][c][lane] = cadd<double>(y1[c], y2[c]);
+    // the loads of the pair after the next, in flight over the barrier and the outer products
+    if (k + 2 * G < npair) p += G * 3 * cs;
+    load_x(nf, nb);
+    // One barrier per step: a wave writes a buffer again two steps later, after a
     // barrier that every wave reaches only when it has read this one.
     __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      chi[c] = cadd<double>(cadd<double>(pk[0][c][lane], pk[1][c][lane]),
-                            cadd<double>(pk[2][c][lane], pk[3][c][lane]));
     // chi already carries the 1/2 of D_oe; the 1/2 of dD_oe and the factor 2 of
     // the variation cancel, so M takes alpha * eta * s with no further factor:
-    //   M_mu(y)    += cf X(y+mu) chi(y)^dag,   cf = -alpha sf
-    //   M_mu(y-mu) += cb chi(y) X(y-mu)^dag,   cb =  alpha sb
-    // with the coefficients folded into chi once per pair.
-    const double cf = -al.a[i] * sf;
-    const double cb = al.a[i] * sb;
+    //   M_mu(y)   = -sf sum alpha X(y+mu) chi(y)^dag
+    //   M_mu(y-mu) = -sb sum alpha chi(y) X(y-mu)^dag
+    // and the sums without -sf, -sb are kept.
+    if (G == 1 || k < npair) {
+      cplx<double> chi[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      cfc[c] = mk<double>(cf * chi[c].x, -cf * chi[c].y);  // cf conj(chi)
-      cbc[c] = cscale<double>(cb, chi[c]);
+      for (int c = 0; c < 3; ++c)
+        chi[c] = cscale<double>(al.a[i],
+                                cadd<double>(cadd<double>(pk[0][c][lane], pk[1][c][lane]),
+                                             cadd<double>(pk[2][c][lane], pk[3][c][lane])));
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+          cfmac<double>(Mf.e[3 * a + b], chi[b], xf[a]);
+          cfmac<double>(Mb.e[3 * a + b], xb[b], chi[a]);
+        }
     }
+    ++j;
+    k += G;
+    i += G;
+    if (i >= nshift) i -= nshift;
+    if (G > 1 && i >= nshift) i -= nshift;
+  };
+  // three register sets and two LDS buffers in turn, without copies
+  cplx<double> xf[3][3], xb[3][3];
+  load_x(xf[0], xb[0]);
+  if (k + G < npair) p += G * 3 * cs;
+  load_x(xf[1], xb[1]);
+  while (true) {
+    pair(xf[0], xb[0], xf[2], xb[2], part[j & 1]);
+    if (j == steps) break;
+    pair(xf[1], xb[1], xf[0], xb[0], part[j & 1]);
+    if (j == steps) break;
+    pair(xf[2], xb[2], xf[1], xb[1], part[j & 1]);
+    if (j == steps) break;
+  }
+  if constexpr (G == 2) {  // group 0 ends with the sum of the forward side, group 1 of the backward
+    double2 (&x)[4][9][64] = *reinterpret_cast<double2 (*)[4][9][64]>(&parts[0][0][0][0][0]);
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+    for (int side = 0; side < 2; ++side) {
+      Su3<double>& M = side == 0 ? Mf : Mb;
+      __syncthreads();
+      if (grp != side)
 #pragma unroll
-      for (int b = 0; b < 3; ++b) {
-        cfma<double>(Mf.e[3 * a + b], xf[a], cfc[b]);
-        cfmac<double>(Mb.e[3 * a + b], xb[b], cbc[a]);  // += cb chi[a] conj(xb[b])
-      }
+        for (int e = 0; e < 9; ++e) x[mu][e][lane] = M.e[e];
+      __syncthreads();
+      if (grp == side)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      xf[c] = nf[c];
-      xb[c] = nb[c];
+        for (int e = 0; e < 9; ++e) M.e[e] = cadd<double>(M.e[e], x[mu][e][lane]);
     }
-    i = i + 1 == nshift ? 0 : i + 1;
   }
   if (!in) return;
-  // the unscaled links for the projection: U = (2 s) U', exactly
+  // U M = (2 s U') (-s M') = -2 U' M'; for the raw M the factor is -s
 #pragma unroll
   for (int e = 0; e < 9; ++e) {
-    Uf.e[e] = cscale<double>(2.0 * sf, Uf.e[e]);
-    Ub.e[e] = cscale<double>(2.0 * sb, Ub.e[e]);
+    Mf.e[e] = cscale<double>(mode == 1 ? -sf : -2.0, Mf.e[e]);
+    Mb.e[e] = cscale<double>(mode == 1 ? -sb : -2.0, Mb.e[e]);
   }
 
   // outputs: forward link at (parity 1, mu, h), backward link at (parity 0, mu, hb)
   for (int side = 0; side < 2; ++side) {
+    if (G == 2 && side != grp) continue;
     const Su3<double>& M = side == 0 ? Mf : Mb;
     const Su3<double>& Ul = side == 0 ? Uf : Ub;
     double2* out = F + (side == 0 ? pstride : 0) + int64_t(mu) * 9 * g.Vh + (side == 0 ? h : hb);
@@ -364,14 +399,19 @@ int lqcd_fermion_force(const lqcd_geom* g, const void* U64, int32_t npf, int32_t
   const KGeom k = make_kgeom(g);
   Alphas al{};
   for (int i = 0; i < nshift; ++i) al.a[i] = alpha[i];
-  const int64_t threads = int64_t(4) * k.Vh;
-  const unsigned grid = unsigned((threads + kForceBlock - 1) / kForceBlock);
-  // small (y, z) tiles keep a site's +-z and +-t neighbours near in launch order:
-  // at 48^4 4 x 4 to 12 x 6 tiles are within 3 %, 2 x 2 tiles 7 % slower
-  const int tz = small_tile(k.Lz), ty = small_tile(k.Ly) ? small_tile(k.Ly) : k.Ly;
-  hipLaunchKernelGGL(k_force, dim3(grid), dim3(kForceBlock), 0, (hipStream_t)stream, k,
-                     (const double2*)U64, (const double2*)X, npf, nshift, al, mode, accumulate,
-                     ty, tz, (double2*)F);
+  const unsigned grid = unsigned((k.Vh + 63) / 64);
+  // (y, z) tiles keep a site's +-z and +-t neighbours near in launch order: 32^4,
+  // 12 pairs, 421 us with 16 x 4 tiles, 440 with 4 x 4; 24^4 144 with 12 x 6, 148
+  // with 6 x 6; 2 x 2 tiles 7 % slower at 48^4
+  const int ty = chunk_tile(k.Ly, 16), tz = chunk_tile(k.Lz, 7);
+  if (k.Vh <= kForceGroupsVh && npf * nshift >= 2)
+    hipLaunchKernelGGL(k_force<2>, dim3(grid), dim3(2 * kForceBlock), 0, (hipStream_t)stream, k,
+                       (const double2*)U64, (const double2*)X, npf, nshift, al, mode, accumulate,
+                       ty, tz, (double2*)F);
+  else
+    hipLaunchKernelGGL(k_force<1>, dim3(grid), dim3(kForceBlock), 0, (hipStream_t)stream, k,
+                       (const double2*)U64, (const double2*)X, npf, nshift, al, mode, accumulate,
+                       ty, tz, (double2*)F);
   LQCD_LAUNCH_CHECK();
   return LQCD_OK;
 }

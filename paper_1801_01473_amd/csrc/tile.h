@@ -26,14 +26,6 @@ __device__ __forceinline__ int tiled_half_index(const KGeom& g, int i, int ty, i
   return inrow + g.Lxh * y0 + g.sz * z + g.st * t;
 }
 
-// A small tile edge: the first of {6, 4, 8, 3, 2} that divides L, else 0
-// (no tiling).
-inline int small_tile(int L) {
-  for (int e : {6, 4, 8, 3, 2})
-    if (L % e == 0 && L > e) return e;
-  return 0;
-}
-
 // A z-slab depth for kernels whose threads are short-lived (every site of a
 // slab's t slice in flight at once): the largest of {8, 6, 4, 3, 2} that
 // divides L, else 0 (no tiling).
