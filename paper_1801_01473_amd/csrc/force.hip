@@ -401,9 +401,11 @@ int lqcd_fermion_force(const lqcd_geom* g, const void* U64, int32_t npf, int32_t
   for (int i = 0; i < nshift; ++i) al.a[i] = alpha[i];
   const unsigned grid = unsigned((k.Vh + 63) / 64);
   // (y, z) tiles keep a site's +-z and +-t neighbours near in launch order: 32^4,
-  // 12 pairs, 421 us with 16 x 4 tiles, 440 with 4 x 4; 24^4 144 with 12 x 6, 148
-  // with 6 x 6; 2 x 2 tiles 7 % slower at 48^4
-  const int ty = chunk_tile(k.Ly, 16), tz = chunk_tile(k.Lz, 7);
+  // 12 pairs, 422 us with 16 x 4 tiles, 440 with 8 x 4; 24^4, 48 pairs, 367 with
+  // 12 x 6, 372 with 8 x 6; but 48^4, 96 pairs, 10.65 ms with 8 x 6 tiles, 11.25
+  // with 16 x 6 (49 and 59 GB read), 32^3 x 48 3.04 and 3.07.
+  const bool large = k.Vh >= 3 << 18 && chunk_tile(k.Ly, 8) >= 4;
+  const int ty = chunk_tile(k.Ly, large ? 8 : 16), tz = chunk_tile(k.Lz, 7);
   if (k.Vh <= kForceGroupsVh && npf * nshift >= 2)
     hipLaunchKernelGGL(k_force<2>, dim3(grid), dim3(2 * kForceBlock), 0, (hipStream_t)stream, k,
                        (const double2*)U64, (const double2*)X, npf, nshift, al, mode, accumulate,
