@@ -22,7 +22,7 @@
 // At 32^3 x 48 with 48 pairs the kernel takes 1.63 ms (1.74 ms with four lanes
 // of one wave per site and two shuffles per pair): 464 M vector instructions
 // keep the FP64 units busy 55 % of the time at the 1.9-2.0 GHz that the card
-// holds under them, 15 GB of loads go through L1 (11 GB from L2, 4.9 GB from
+// holds under them, 15 GB of loads go through L1 (11 GB from L2, 5.2 GB from
 // memory against 2.7 GB that must be read).  With every X read from L2 it would
 // take 1.42 ms.  Two lanes per link at twice the waves (1.67 ms), loads one pair
 // ahead (1.63 ms, but 3 % slower where few waves are in flight), the next pair's
@@ -403,7 +403,7 @@ int lqcd_fermion_force(const lqcd_geom* g, const void* U64, int32_t npf, int32_t
   // (y, z) tiles keep a site's +-z and +-t neighbours near in launch order: 32^4,
   // 12 pairs, 422 us with 16 x 4 tiles, 440 with 8 x 4; 24^4, 48 pairs, 367 with
   // 12 x 6, 372 with 8 x 6; but 48^4, 96 pairs, 10.65 ms with 8 x 6 tiles, 11.25
-  // with 16 x 6 (49 and 59 GB read), 32^3 x 48 3.04 and 3.07.
+  // with 16 x 6 (45 and 59 GB read), 32^3 x 48 3.04 and 3.07.
   const bool large = k.Vh >= 3 << 18 && chunk_tile(k.Ly, 8) >= 4;
   const int ty = chunk_tile(k.Ly, large ? 8 : 16), tz = chunk_tile(k.Lz, 7);
   if (k.Vh <= kForceGroupsVh && npf * nshift >= 2)

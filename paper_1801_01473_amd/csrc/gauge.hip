@@ -160,8 +160,8 @@ __global__ void __launch_bounds__(kGaugeBlock) k_gauge_force(KGeom g, const doub
 
 // F (+)= -beta/3 TA(U A), A the plaquette staples: the whole force without
 // rectangles.  48^4: 3.1 ms, 24^3 x 48: 0.38 ms (6.0 and 0.63 with one thread per
-// link in k_gauge_force's order, 19 matrices per link against 14 here).  Bound by
-// the matrices that pass from L2 to the workgroups, as the smearing.
+// link in k_gauge_force's order, 19 matrices per link against 14 here).  Bound as
+// the smearing.
 __global__ void __launch_bounds__(256, 2) k_plaquette_force(KGeom g, const double2* __restrict__ U,
                                                             double beta, int accumulate, int ty,
                                                             int tz, double2* __restrict__ F) {

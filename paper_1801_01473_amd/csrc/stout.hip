@@ -136,9 +136,12 @@ __device__ __forceinline__ M3 evaluate(const Poly& f, const Alg& x, const Herm& 
 }
 
 // One level: U' = exp(X) U.  24^3 x 32: 0.27 ms (0.43 with the directions as
-// separate segments of the grid and a Taylor exponential).  Bound by the 14
-// link matrices per link that pass from L2 to the workgroups, 3.6 GB at about
-// 12 TB/s; its HBM bytes would take 0.11 ms, its products 0.12 ms.
+// separate segments of the grid and a Taylor exponential).  Bound by waiting for
+// 14 link matrices per link at the 8 waves a CU that registers and LDS allow:
+// 3.6 GB from L2 (13 TB/s; a kernel that only reads L2 reaches 30), a quarter of
+// the requests missing it, FP64 units 45 % busy.  Its HBM bytes would take 0.11 ms,
+// its products 0.12 ms.  Only the sites' own links in LDS, for 12 waves a CU, made
+// the plaquette force, which loads the same, 8 % slower.
 __global__ void __launch_bounds__(256, 2) k_stout_smear(KGeom g, const double2* __restrict__ U,
                                                         double rho, int ty, int tz,
                                                         double2* __restrict__ out) {
