@@ -30,7 +30,7 @@
 // at 6.5 TB/s: the sites in flight on an XCD have 9 MB of fields, links and
 // forces), so the links that the waves of a workgroup share go through LDS
 // (4.5 -> 3.7 ms).
-// 48^4: 25.6 ms with stored staples, 7.2 ms now.
+// 48^4: 25.6 ms with stored staples, 7.1 ms now.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -103,14 +103,30 @@ __device__ __forceinline__ Alg ld_alg(const double2* __restrict__ P, const Plane
   return Alg{p[0], p[n], p[2 * n], p[3 * n]};
 }
 
+// Stores past the caches (NT) where the fields of a pass exceed the 256 MB
+// last-level cache, so that they leave the links there: 48^4 3.59 -> 3.44 ms in
+// k_loops, 3.73 -> 3.66 in k_loop_force; smaller lattices read both back from it.
+constexpr int64_t kStreamFieldBytes = int64_t(256) << 20;
+
+template <bool NT>
+__device__ __forceinline__ void st(double2* p, double2 v) {
+  if constexpr (NT) {
+    typedef double V2 __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store(V2{v.x, v.y}, reinterpret_cast<V2*>(p));
+  } else {
+    *p = v;
+  }
+}
+
+template <bool NT>
 __device__ __forceinline__ void st_alg(double2* __restrict__ P, const Planes& pl, int slot, int f,
                                        int par, int h, const Alg& a) {
   double2* p = field_at(P, pl, slot, f, par, h);
   const int n = 1 << pl.sh;
-  p[0] = a.o01;
-  p[n] = a.o02;
-  p[2 * n] = a.o12;
-  p[3 * n] = a.d;
+  st<NT>(p, a.o01);
+  st<NT>(p + n, a.o02);
+  st<NT>(p + 2 * n, a.o12);
+  st<NT>(p + 3 * n, a.d);
 }
 
 // What a wave of the plane kernels works with: one plane of 64 sites of one
@@ -152,6 +168,7 @@ __device__ __forceinline__ PlaneSite plane_site(const KGeom& g, const double2* _
 }
 
 // One workgroup per 64 half indices of both parities, wave = plane.
+template <bool NT>
 __global__ void __launch_bounds__(768, 3) k_loops(KGeom g, const double2* __restrict__ U,
                                                   const Planes pl, double w0, double w1, int ty,
                                                   int tz, double2* __restrict__ P) {
@@ -174,7 +191,7 @@ __global__ void __launch_bounds__(768, 3) k_loops(KGeom g, const double2* __rest
     const M3 e = lds_mul(sh[1][a], lane, ld_m3(p.b_s, p.a2, g.Vh));
     const M3 l = lds_mul(sh[0][a], lane, e);  // a, a, b
     const Alg ra = ta_mul_dag(l, r);
-    st_alg(P, pl, task, 1, cs.par, p.h, ra);
+    st_alg<NT>(P, pl, task, 1, cs.par, p.h, ra);
     a_axpy(w1, ra, sum);
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -183,10 +200,10 @@ __global__ void __launch_bounds__(768, 3) k_loops(KGeom g, const double2* __rest
     const M3 e = lds_mul(sh[1][b], lane, ld_m3(p.a_s, p.b2, g.Vh));
     const M3 r = lds_mul(sh[0][b], lane, e);  // b, b, a
     const Alg rb = ta_mul_dag(l, r);
-    st_alg(P, pl, task, 2, cs.par, p.h, rb);
+    st_alg<NT>(P, pl, task, 2, cs.par, p.h, rb);
     a_axpy(w1, rb, sum);
   }
-  st_alg(P, pl, task, 0, cs.par, p.h, sum);
+  st_alg<NT>(P, pl, task, 0, cs.par, p.h, sum);
 }
 
 // Re Tr[a b^dag]
@@ -238,6 +255,7 @@ __global__ void __launch_bounds__(768, 3) k_loop_action(KGeom g, const double2* 
 // One workgroup per 64 half indices of one parity, wave = direction a.  The
 // links U_mu(x - mu), U_mu(x - 2 mu) of the transports, which three or four
 // waves use, go through LDS: 20 link matrices per site from L2 instead of 40.
+template <bool NT>
 __global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* __restrict__ U,
                                                        const double2* __restrict__ P,
                                                        const Planes pl, double w1, int ty,
@@ -293,7 +311,7 @@ __global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* _
       z.x += o.x;
       z.y += o.y;
     }
-    out[int64_t(e) * g.Vh] = z;
+    st<NT>(out + int64_t(e) * g.Vh, z);
   }
 }
 
@@ -384,11 +402,12 @@ int lqcd_gauge_force_staples(const lqcd_geom* g, const void* U64, double beta, d
   for (int lo = 0; lo < 6; lo += step) {
     Planes p = plane_pass(lo, lo + step, accumulate, &seen);
     p.sh = chunk_shift(k.Vh);
-    hipLaunchKernelGGL(k_loops, dim3(chunk_pair_blocks(k.Vh)), dim3(128 * p.n), 0, s, k, U, p, w0, w1,
-                       ty, tz, P);
+    const bool nt = int64_t(p.n) * int64_t(kPlaneBytes) * k.Vh > kStreamFieldBytes;
+    hipLaunchKernelGGL(nt ? k_loops<true> : k_loops<false>, dim3(chunk_pair_blocks(k.Vh)),
+                       dim3(128 * p.n), 0, s, k, U, p, w0, w1, ty, tz, P);
     LQCD_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_loop_force, dim3(chunk_blocks(k.Vh)), dim3(256), 0, s, k, U, P, p, w1,
-                       ty, tz, out);
+    hipLaunchKernelGGL(nt ? k_loop_force<true> : k_loop_force<false>, dim3(chunk_blocks(k.Vh)),
+                       dim3(256), 0, s, k, U, P, p, w1, ty, tz, out);
     LQCD_LAUNCH_CHECK();
   }
   return LQCD_OK;
