@@ -70,8 +70,11 @@ __global__ void __launch_bounds__(kSplitBlock) k_dslash_split(const DslashCall a
     }
   }
   if (halt || !any) {  // uniform over the block; one round trip for all flags
-    if (MODE == DM_CG && a.sys && blk == 0 && threadIdx.x < B && rhs0 + int(threadIdx.x) < a.nrhs)
-      a.sys[rhs0 + threadIdx.x].upd_any = 0;  // finished systems: no update follows
+    if (MODE == DM_CG && a.sys && blk == 0 && threadIdx.x < B && rhs0 + int(threadIdx.x) < a.nrhs) {
+      SysState& S = a.sys[rhs0 + threadIdx.x];  // finished systems: no update follows
+      S.upd_any = 0;
+      S.restart = 0;
+    }
     return;
   }
 

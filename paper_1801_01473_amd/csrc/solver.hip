@@ -209,6 +209,8 @@ __global__ void __launch_bounds__(kScalarThreads) k_sc_init(
       S.upd_any = 0;
       S.r2ref = rr;
       S.rho_iter = rr;
+      S.rho_k = rr;
+      S.iter_k = 0;
       S.restart = 0;
       S.iters64 = 0;
       S.wpos = 0;
@@ -303,22 +305,6 @@ struct FusedBeta {
   double red[K][kScalarThreads / 64];
   BetaShared sh;
 };
-
-struct BaseStep {
-  bool go;
-  double zs, bs;  // p = zs r + bs p  (fused: bs = |r|^2 / bs, once |r|^2 is known)
-  int slot;       // ring slot of the new residual (before % R)
-};
-
-__device__ __forceinline__ BaseStep base_step(const SysState& S, int base, bool fused) {
-  if (fused) return BaseStep{S.upd_any != 0, S.zeta_new[base], S.rho_k, S.iter_k + 1};
-  return BaseStep{S.upd_any != 0, S.zeta[base], S.b_s[base], S.iters};
-}
-
-__device__ __forceinline__ void finish_step(BaseStep& u, double rr) {
-  u.go = u.go && finite_d(rr);
-  u.bs = rr / u.bs;
-}
 
 // K5: x_s += a_s p_s ; p_s = zeta_s r + beta_s p_s for the shifts updated this
 // iteration (FB: a single shift)

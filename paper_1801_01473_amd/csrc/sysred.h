@@ -134,6 +134,27 @@ __device__ __forceinline__ void store_step(SysState& S, GlobalFlags* gf, int nsh
   }
 }
 
+// What an update of the base direction takes from the state.  Fused: what the
+// step length left there; a system that was finished before its first iteration
+// (a zero right-hand side beside others) never had one, and the loads from the
+// residual ring are issued before `go` is looked at, so its slot is 0.
+struct BaseStep {
+  bool go;
+  double zs, bs;  // p = zs r + bs p  (fused: bs = |r|^2 / bs, once |r|^2 is known)
+  int slot;       // ring slot of the new residual (before % R), never negative
+};
+
+__host__ __device__ __forceinline__ BaseStep base_step(const SysState& S, int base, bool fused) {
+  const bool go = S.upd_any != 0;
+  if (fused) return BaseStep{go, S.zeta_new[base], S.rho_k, go ? S.iter_k + 1 : 0};
+  return BaseStep{go, S.zeta[base], S.b_s[base], S.iters};
+}
+
+__device__ __forceinline__ void finish_step(BaseStep& u, double rr) {
+  u.go = u.go && rr == rr && fabs(rr) <= 1.7e308;
+  u.bs = rr / u.bs;
+}
+
 // The state after the residual norm rr is known, by a whole workgroup: thread s
 // advances shift s, then every thread its share of the window coefficients
 // (wc, deferred shift updates):
