@@ -1156,6 +1156,7 @@ int launch_iteration(const Ctx& c, const Core& k, const Phase& ph, hipStream_t s
   ba.rel_delta2 = ph.rel_d2;
   ba.sw2 = ph.sw2;
   ba.fp64 = ph.prec == LQCD_F64 ? 1 : 0;
+  ba.fused = ph.fused ? 1 : 0;
   ba.wc = win ? c.at<WinCoef>(c.L.wc) : nullptr;
   ba.win = k.win;
   const double* part_r = c.at<double>(c.L.pr);

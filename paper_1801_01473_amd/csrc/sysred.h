@@ -101,7 +101,8 @@ __device__ __forceinline__ bool cg_step(const StepState& S, double tt, double pp
 
 // The state after the step length is known, by kMaxShift threads of one
 // wavefront: s in [0, kMaxShift) is the thread's number (others do nothing) and
-// the shift it advances.
+// the shift it advances.  Other workgroups of the launch may read rho, m2s, done
+// and live: none is stored here, an error ends the system in store_beta.
 __device__ __forceinline__ void store_step(SysState& S, GlobalFlags* gf, int nshift, bool ok,
                                            bool err, double a, double pp, int s) {
   if (s < 0 || s >= kMaxShift) return;
@@ -128,8 +129,6 @@ __device__ __forceinline__ void store_step(SysState& S, GlobalFlags* gf, int nsh
   if (ok) S.a = a;
   if (err) {
     S.err = 1;
-    S.done = 1;
-    S.live = 0;
     gf->error = 1;
   }
 }
@@ -161,14 +160,14 @@ __device__ __forceinline__ void finish_step(BaseStep& u, double rr) {
 //   x_s += a_s p_s   ->  cx_s += a_s cp_s
 //   p_s  = zeta_s r + b_s p_s  ->  cp_s = b_s cp_s, cp_s[n+1] = zeta_s
 // where index n+1 is the residual after this iteration (ring slot n).  S.rho_k,
-// S.iter_k, S.zeta_new and (unless rr is not finite, which every workgroup sees)
-// S.upd_any stay as the step length left them, so other workgroups of the same
-// launch may read those.
+// S.iter_k, S.zeta_new and (fused) S.upd_any stay as the step length left them, so
+// other workgroups of the same launch may read those.
 struct BetaArgs {
   int max_iter = 0;
   double rel_delta2 = 0.0;  // reliable-update trigger
   double sw2 = 0.0;         // FP64 -> FP32 switch level
   int fp64 = 0;             // arithmetic of this phase
+  int fused = 0;            // the launch's other workgroups update the base direction
   WinCoef* wc = nullptr;    // window coefficients of every system, or none
   int win = 1;
 };
@@ -213,10 +212,12 @@ __device__ __forceinline__ void store_beta(SysState& S, GlobalFlags* gf, int nsh
       sh.n = -1;
       if (bad) {
         S.err = 1;
+        if (!ba.fused) S.upd_any = 0;
+        gf->error = 1;
+      }
+      if (S.err) {  // found here or by the step length
         S.done = 1;
         S.live = 0;
-        S.upd_any = 0;
-        gf->error = 1;
       }
       if (go) {
         S.a_old = a_step;
