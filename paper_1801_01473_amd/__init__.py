@@ -19,6 +19,8 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import threading
+import weakref
 from dataclasses import dataclass
 
 import torch
@@ -192,6 +194,10 @@ def _stream() -> int:
     if _raw_stream is None or _device is None or not torch.cuda.is_initialized():
         return torch.cuda.current_stream().cuda_stream
     return _raw_stream(_device())
+
+
+def _capturing() -> bool:
+    return torch.cuda.is_initialized() and torch.cuda.is_current_stream_capturing()
 
 
 def _ptr(t: torch.Tensor | None) -> int:
@@ -443,21 +449,56 @@ def solver_workspace_bytes(geom: Geometry, params: SolverParams, nshift: int, nr
     return int(_fn("lqcd_solver_workspace_bytes")(geom.c(), ctypes.byref(params), nshift, nrhs))
 
 
-_ws_cache = {}
+class _Workspaces(dict):
+    """The workspaces of one thread, by (device, stream).  A call that returns
+    before its kernels have run leaves them reading its workspace, so only calls
+    ordered behind them -- on the same stream -- may use it again; and two threads
+    may be inside calls on one stream at once.  They go with the thread."""
+
+    __hash__ = object.__hash__
+
+
+_ws_local = threading.local()
+_ws_all = weakref.WeakSet()  # every thread's
+_ws_lock = threading.Lock()
+
+
+def _workspaces() -> _Workspaces:
+    ws = getattr(_ws_local, "ws", None)
+    if ws is None:
+        ws = _ws_local.ws = _Workspaces()
+        with _ws_lock:
+            _ws_all.add(ws)
+    return ws
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
-    key = str(device)
-    ws = _ws_cache.get(key)
+    """At least nbytes for a call on the current stream: kept for the next ones, so
+    that iteration graphs find it at the same address.  A captured call gets memory
+    of the capture's own."""
+    if _capturing():
+        return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    pool, key = _workspaces(), (device, _stream())
+    ws = pool.get(key)
     if ws is None or ws.numel() < nbytes:
-        _ws_cache[key] = None
-        ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-        _ws_cache[key] = ws
+        ws = None
+        pool.pop(key, None)
+        try:
+            ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            release_workspace()  # what other streams and threads keep
+            ws = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        pool[key] = ws
     return ws
 
 
 def release_workspace() -> None:
-    _ws_cache.clear()
+    """Drops the workspaces that every thread keeps (calls still running on the GPU
+    finish with theirs)."""
+    with _ws_lock:
+        pools = list(_ws_all)
+    for pool in pools:
+        pool.clear()
 
 
 def cg(geom: Geometry, params: SolverParams, U64, b, x=None, sigma=0.0, Uinner=None,
