@@ -492,6 +492,19 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return ws
 
 
+def _workspace_twice(nbytes: int, device) -> torch.Tensor:
+    """2 nbytes where that costs nothing that stays -- the kept workspace if it is
+    that large, else memory that goes back to torch's allocator with the call --
+    and the kept workspace of nbytes where so much is not there."""
+    ws = None if _capturing() else _workspaces().get((device, _stream()))
+    if ws is not None and ws.numel() >= 2 * nbytes:
+        return ws
+    try:
+        return torch.empty(2 * nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return _workspace(nbytes, device)
+
+
 def release_workspace() -> None:
     """Drops the workspaces that every thread keeps (calls still running on the GPU
     finish with theirs)."""
@@ -751,8 +764,8 @@ def gauge_force(geom: Geometry, U64, beta: float, c1: float = SYMANZIK_C1, out=N
     elif method == "staples":
         # twice the required size lets the library form the loops of all six
         # planes in one pass and write the force once
-        nbytes = 2 * int(_fn("lqcd_gauge_force_staples_workspace_bytes")(geom.c()))
-        ws = _workspace(nbytes, U64.device)
+        nbytes = int(_fn("lqcd_gauge_force_staples_workspace_bytes")(geom.c()))
+        ws = _workspace_twice(nbytes, U64.device)
         _check(_fn("lqcd_gauge_force_staples")(geom.c(), _ptr(U64), float(beta), float(c1),
                                                1 if accumulate else 0, _ptr(out), _ptr(ws),
                                                ws.numel(), _stream()))

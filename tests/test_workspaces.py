@@ -61,3 +61,22 @@ def test_release_and_out_of_memory(stream, monkeypatch):
     monkeypatch.setattr(torch, "empty", limited)
     ws = lq._workspace(2000, CPU)
     assert failed == [2000] and ws.numel() >= 2000
+
+
+def test_twice_the_size_is_not_kept(stream, monkeypatch):
+    """Twice a size comes from the kept workspace or is given back; without the
+    memory for it, the size itself."""
+    ws = lq._workspace_twice(1000, CPU)
+    assert ws.numel() == 2000 and not lq._workspaces()
+    kept = lq._workspace(3000, CPU)
+    assert lq._workspace_twice(1000, CPU).data_ptr() == kept.data_ptr()
+    lq.release_workspace()
+    empty = torch.empty
+
+    def limited(n, **k):
+        if n > 1500:
+            raise torch.OutOfMemoryError("limit")
+        return empty(n, **k)
+
+    monkeypatch.setattr(torch, "empty", limited)
+    assert 1000 <= lq._workspace_twice(1000, CPU).numel() < 2000
