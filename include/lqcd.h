@@ -446,7 +446,9 @@ int lqcd_gauge_force(const lqcd_geom *g, const void *U64, double beta, double c1
  * traceless anti-Hermitian parts of the plaquette and of the two rectangles
  * at every site are stored in the workspace, and each staple of a link is
  * then one of those matrices moved along the loop by single links (about 29
- * SU(3) products per link instead of 85; the links must be unitary).
+ * SU(3) products per link instead of 85).  That holds along unitary links: a
+ * link of F next to one whose rows are not orthonormal to 2^-46 has its staples
+ * multiplied out, so any links are accepted, at the speed of lqcd_gauge_force.
  * ws must hold lqcd_gauge_force_staples_workspace_bytes(g) bytes (576 B per
  * site, three planes at a time) and not alias U64 or F; given twice that, all
  * six planes are formed at once and F is written once.  Equal to

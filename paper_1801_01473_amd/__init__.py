@@ -753,7 +753,8 @@ def gauge_action(geom: Geometry, U64, beta: float, c1: float = SYMANZIK_C1) -> f
 def gauge_force(geom: Geometry, U64, beta: float, c1: float = SYMANZIK_C1, out=None,
                 accumulate=False, method: str = "staples"):
     """F = TA(U M) of S_g, packed like the links; accumulate adds into out.
-    method "staples": through the stored loops of each plane (workspace);
+    method "staples": through the stored loops of each plane (workspace), except
+    next to links that are not unitary to 2^-46, where staples are multiplied out;
     "direct": every staple of every link multiplied out in place."""
     _u64_arg(geom, U64)
     out = empty_links(geom, F64, LINKS18, U64.device) if out is None else out

@@ -8,7 +8,8 @@
 // closed loops at x, of which only the traceless anti-Hermitian part TA is
 // needed: F_a(x) = -(beta/3) sum of w TA(loop at x that starts along a) over
 // the loops through the link (x, a), and TA commutes with moving a loop's
-// base point, TA(V^dag W V) = V^dag TA(W) V for unitary V.  Every loop through
+// base point, TA(V^dag W V) = V^dag TA(W) V for unitary V (a site near a link that
+// is not unitary to rounding has its staples multiplied out instead).  Every loop through
 // (x, a) is one of l, ra, rb based at x, x-a, x-b, x-2b or x-a-b, moved to x
 // along its own links, reversed (sign -) where (x, a) is its upper side:
 //   F_a/(-beta/3) = c0 l(x) + c1 (ra(x) + rb(x))
@@ -252,15 +253,94 @@ __global__ void __launch_bounds__(768, 3) k_loop_action(KGeom g, const double2* 
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
+// Whether a link's rows are orthonormal to rounding (2^-46: links of one update or
+// exponential are within some 2^-50, and drift as the root of the products taken).
+// A transport V^dag TA(W) V stands for TA(V^-1 W V), so it may only pass along such
+// links; an error of d in V^dag V would enter the force about six times.
+__device__ __forceinline__ bool unitary(const M3& u) {
+  constexpr double kTol = 0x1p-46;
+  double worst = 0.0;
+#pragma unroll
+  for (int i = 0; i < 9; i += 3) {
+    double n = -1.0;
+#pragma unroll
+    for (int e = i; e < i + 3; ++e) n = fma(u.e[e].x, u.e[e].x, fma(u.e[e].y, u.e[e].y, n));
+    double2 d = make_double2(0.0, 0.0);
+    const int j = (i + 3) % 9;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) cfmac<double>(d, u.e[i + e], u.e[j + e]);
+    worst += fabs(n) + fabs(d.x) + fabs(d.y);  // (a sum: NaN stays)
+  }
+  return worst <= kTol;
+}
+
+// TA of U_a(x) times the weighted staples of the link (x, a) in its plane with b,
+// each multiplied out along its path from x + a to x: for the sites whose loops
+// cannot be moved along their links (all of them, single-precision links: 48^4
+// 24.1 ms, 8^4 94 us; one link of 8^4 135 us, a chain of 108 steps).  The steps of a path, two bits each from the lowest:
+// 0 +a, 1 +b, 2 -a, 3 -b; the paths below the link have b reversed.
+__device__ __forceinline__ Alg direct_loops(const KGeom& g, const double2* __restrict__ U,
+                                            const C4& x, int par, int a, int b, double w0,
+                                            double w1) {
+  constexpr int kSteps[4] = {
+      1 | 2 << 2 | 3 << 4,                        // +b -a -b
+      0 | 1 << 2 | 2 << 4 | 2 << 6 | 3 << 8,      // +a +b -a -a -b
+      1 | 2 << 2 | 2 << 4 | 3 << 6 | 0 << 8,      // +b -a -a -b +a
+      1 | 1 << 2 | 2 << 4 | 3 << 6 | 3 << 8,      // +b +b -a -b -b
+  };
+  M3 sum = m_zero();
+#pragma unroll 1
+  for (int k = 0; k < 8; ++k) {
+    const int q = k >> 1;
+    int code = q == 0 ? kSteps[0] : q == 1 ? kSteps[1] : q == 2 ? kSteps[2] : kSteps[3];
+    M3 t = m_unit();
+    C4 s = shift(g, x, a, 1);
+    int p = 1 - par;
+#pragma unroll 1
+    for (int n = q == 0 ? 3 : 5; n > 0; --n, code >>= 2) {
+      const int mu = code & 1 ? b : a;
+      const bool back = ((code >> 1) ^ (code & k & 1)) & 1;
+      if (back) s = shift(g, s, mu, -1);
+      const M3 u = ld_m3(link_res(g, U, back ? 1 - p : p, mu), half_index(g, s), g.Vh);
+#pragma unroll
+      for (int i = 0; i < 9; i += 3) {  // row by row, in place
+        double2 r[3];
+        if (back) {
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            r[j] = cmulc<double>(u.e[3 * j], t.e[i]);
+            cfmac<double>(r[j], u.e[3 * j + 1], t.e[i + 1]);
+            cfmac<double>(r[j], u.e[3 * j + 2], t.e[i + 2]);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            r[j] = cmul<double>(t.e[i], u.e[j]);
+            cfma<double>(r[j], t.e[i + 1], u.e[3 + j]);
+            cfma<double>(r[j], t.e[i + 2], u.e[6 + j]);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) t.e[i + j] = r[j];
+      }
+      if (!back) s = shift(g, s, mu, 1);
+      p = 1 - p;
+    }
+    m_axpy(q == 0 ? w0 : w1, t, sum);
+  }
+  return ta(m_mul(ld_m3(link_res(g, U, par, a), half_index(g, x), g.Vh), sum), 1.0);
+}
+
 // One workgroup per 64 half indices of one parity, wave = direction a.  The
 // links U_mu(x - mu), U_mu(x - 2 mu) of the transports, which three or four
 // waves use, go through LDS: 20 link matrices per site from L2 instead of 40.
 template <bool NT>
 __global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* __restrict__ U,
                                                        const double2* __restrict__ P,
-                                                       const Planes pl, double w1, int ty,
-                                                       int tz, double2* __restrict__ F) {
+                                                       const Planes pl, double w0, double w1,
+                                                       int ty, int tz, double2* __restrict__ F) {
   __shared__ double2 sh[4][2][9][64];  // U_mu(x - mu), U_mu(x - 2 mu)
+  __shared__ bool movable[4][64];      // loops can be moved along both
   const ChunkSite cs = chunk_site(g, ty, tz);
   const int h = cs.h, par = cs.par, opp = 1 - par, lane = cs.lane, a = cs.task;
   const C4 x = site_c4(g, h, par);
@@ -273,8 +353,10 @@ __global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* _
       sh[a][0][e][lane] = u1.e[e];
       sh[a][1][e][lane] = u2.e[e];
     }
+    movable[a][lane] = unitary(u1) & unitary(u2);
   }
   __syncthreads();
+  bool ok = movable[0][lane] & movable[1][lane] & movable[2][lane] & movable[3][lane];
   const int am = axis(g, x, a).off(-1);
   Alg f = a_zero(), q = a_zero();
 #pragma unroll 1
@@ -294,12 +376,19 @@ __global__ void __launch_bounds__(256, 2) k_loop_force(KGeom g, const double2* _
     a_axpy(-sg, z, f);
     a_axpy(sg, ld_alg(P, pl, s, 0, par, h), f);
     a_axpy(sg, ld_alg(P, pl, s, fa, opp, h + am), q);
-    y = transport(ld_m3(link_res(g, U, par, b), hb + am, g.Vh),
-                  ld_alg(P, pl, s, fa, par, hb + am));
+    const M3 v = ld_m3(link_res(g, U, par, b), hb + am, g.Vh);
+    y = transport(v, ld_alg(P, pl, s, fa, par, hb + am));
+    ok = ok & unitary(v);
     a_axpy(-sg, y, q);
   }
   if (!cs.in || !((pl.dirs >> a) & 1)) return;
   a_axpy(w1, transport(lds_m3(sh[a][0], lane), q), f);
+  if (!ok) {
+    f = a_zero();
+#pragma unroll 1
+    for (int b = 0; b < 4; ++b)
+      if (b != a && pl.slot[a][b] >= 0) a_axpy(1.0, direct_loops(g, U, x, par, a, b, w0, w1), f);
+  }
   double2* out = F + (int64_t(par) * 4 + a) * 9 * g.Vh + h;
   const M3 v = a_full(f);
   const bool add = (pl.add >> a) & 1;
@@ -407,7 +496,7 @@ int lqcd_gauge_force_staples(const lqcd_geom* g, const void* U64, double beta, d
                        dim3(128 * p.n), 0, s, k, U, p, w0, w1, ty, tz, P);
     LQCD_LAUNCH_CHECK();
     hipLaunchKernelGGL(nt ? k_loop_force<true> : k_loop_force<false>, dim3(chunk_blocks(k.Vh)),
-                       dim3(256), 0, s, k, U, P, p, w1, ty, tz, out);
+                       dim3(256), 0, s, k, U, P, p, w0, w1, ty, tz, out);
     LQCD_LAUNCH_CHECK();
   }
   return LQCD_OK;

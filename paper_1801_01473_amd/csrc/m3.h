@@ -98,10 +98,14 @@ __device__ __forceinline__ C4 shift(const KGeom& g, C4 s, int mu, int d) {
   return s;
 }
 
+__device__ __forceinline__ int half_index(const KGeom& g, const C4& s) {
+  return (s.x >> 1) + g.Lxh * (s.y + g.Ly * (s.z + g.Lz * s.t));
+}
+
 __device__ __forceinline__ M3 link(const KGeom& g, const double2* __restrict__ U, const C4& s,
                                    int mu) {
   const int par = (s.x + s.y + s.z + s.t) & 1;
-  const int h = (s.x >> 1) + g.Lxh * (s.y + g.Ly * (s.z + g.Lz * s.t));
+  const int h = half_index(g, s);
   const double2* p = U + (int64_t(par) * 4 + mu) * 9 * int64_t(g.Vh) + h;
   M3 r;
 #pragma unroll
