@@ -70,7 +70,7 @@ int dslash_launch(const DslashCall& c, const DslashCfg& cfg, hipStream_t st) {
 
 namespace {
 
-using TuneKey = std::tuple<int, int, int, int, int, int, int, int, int, int>;
+using TuneKey = std::tuple<int, int, int, int, int, int, int, int, int, int, int>;
 std::mutex g_tune_mu;
 std::map<TuneKey, DslashCfg> g_tune;
 
@@ -100,8 +100,9 @@ bool tuning_verbose() {
 // One line per tuned shape:
 // "<key>;<block>,<B>,<xcd>,<tz>,<nt>,<occ>,<ilv>,<lf>,<hh>,<ty>[,<ns>[,<tm>,<tp>[,<sp>]]]"
 // where the key names the cache format, the GPU architecture and CU count,
-// the geometry, precision, link format, RHS count, forced RHS block and
-// mode.  Lines that do not parse, or whose configuration is not valid for
+// the geometry, precision, link format, RHS count, forced RHS block, mode,
+// pairs and, where it matters (separate_scalars), a solve whose scalars stay
+// in kernels of their own.  Lines that do not parse, or whose configuration is not valid for
 // the shape, are ignored (that shape is tuned again).
 constexpr int kTuneCacheFormat = 1;
 
@@ -115,16 +116,26 @@ constexpr int kSplitMaxVh = 1 << 18;
 // 55 us on one field but 74 on three in turn, against 57 and 67 in pairs.
 constexpr int kSplitOncePerRhsVh = 1 << 16;
 
-// What the split kernel saves elsewhere when it can take over the step length
-// (fused_partials_pay): the one-workgroup kernels of the scalars, 5
-// and 4 us a launch at 16^4, against about 1 us more in the CG kernels each.
-// Its times in CG mode are ranked with this credit.
+// What the split kernel saves elsewhere when the solve takes its scalars into the
+// CG kernels (DslashCall::fusable, fused_partials_pay): their one-workgroup kernels,
+// 5 and 4 us a launch at 16^4, against about 1 us more in the CG kernels each.  Its
+// times in CG mode are ranked with this credit.
 constexpr float kFusedCreditMs = 0.006f;
+
+bool credit_applies(const DslashCall& c) {
+  return c.mode == DM_CG && fused_partials_pay((c.g.Vh + 63) / 64, c.nrhs);
+}
+
+// A CG update that the credit would apply to, of a solve that cannot use it: tuned
+// and kept apart from those that can.
+bool separate_scalars(const DslashCall& c) { return credit_applies(c) && !c.fusable; }
 
 const char* tune_cache_path() {
   const char* e = std::getenv("LQCD_TUNE_CACHE");
   return (e && e[0]) ? e : nullptr;
 }
+
+constexpr char kSeparateSuffix[] = "/sep";
 
 std::string tune_cache_key(const DslashCall& c, int forced) {
   int dev = 0;
@@ -138,9 +149,10 @@ std::string tune_cache_key(const DslashCall& c, int forced) {
   for (char& ch : arch)
     if (ch == ';' || ch == ' ') ch = '_';
   char buf[256];
-  std::snprintf(buf, sizeof(buf), "v%d/%s/%dcu/%dx%dx%dx%d/p%d/f%d/n%d/b%d/m%d%s", kTuneCacheFormat,
-                arch.c_str(), cus, c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, c.prec, c.fmt, c.nrhs, forced,
-                c.mode, c.pairs ? "/pairs" : "");
+  std::snprintf(buf, sizeof(buf), "v%d/%s/%dcu/%dx%dx%dx%d/p%d/f%d/n%d/b%d/m%d%s%s",
+                kTuneCacheFormat, arch.c_str(), cus, c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, c.prec, c.fmt,
+                c.nrhs, forced, c.mode, c.pairs ? "/pairs" : "",
+                separate_scalars(c) ? kSeparateSuffix : "");
   return buf;
 }
 
@@ -158,24 +170,27 @@ bool cfg_valid(const DslashCall& c, const DslashCfg& f, int forced) {
          (!c.pairs || (f.rhs_block % 2 == 0 && f.tm == 0 && f.mf == 0));
 }
 
-// The last valid entry for the key, if any.
+// The last valid entry for the key, if any.  A line of the solves with the credit in
+// which another kernel won all the same holds for those without it.
 bool tune_cache_lookup(const char* path, const std::string& key, const DslashCall& c, int forced,
                        DslashCfg* out) {
   FILE* f = std::fopen(path, "r");
   if (!f) return false;
+  const bool sep = separate_scalars(c);
+  const std::string with_credit = sep ? key.substr(0, key.size() - std::strlen(kSeparateSuffix)) : key;
   char line[512];
   bool found = false;
   while (std::fgets(line, sizeof(line), f)) {
     char* semi = std::strchr(line, ';');
     if (!semi) continue;
     *semi = '\0';
-    if (key != line) continue;
+    if (key != line && with_credit != line) continue;
     DslashCfg v;
     const int n = std::sscanf(semi + 1, "%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d,%d", &v.block,
                               &v.rhs_block, &v.xcd, &v.tz, &v.nt, &v.occ, &v.ilv, &v.lf, &v.hh,
                               &v.ty, &v.ns, &v.tm, &v.tp, &v.sp);
     if (n != 10 && n != 11 && n != 13 && n != 14) continue;
-    if (!cfg_valid(c, v, forced)) continue;
+    if (!cfg_valid(c, v, forced) || (key != line && v.sp == 1)) continue;
     *out = v;
     found = true;
   }
@@ -230,7 +245,8 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
       return LQCD_OK;
     }
   }
-  const TuneKey key{c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, c.prec, c.fmt, c.nrhs, forced, c.mode, c.pairs};
+  const TuneKey key{c.g.Lx, c.g.Ly, c.g.Lz,  c.g.Lt, c.prec, c.fmt,
+                    c.nrhs, forced, c.mode, c.pairs, separate_scalars(c) ? 1 : 0};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(key);
@@ -367,10 +383,8 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     return LQCD_OK;
   };
 
-  const bool fusable = cg && fused_partials_pay((c.g.Vh + 63) / 64, c.nrhs);
-  auto ranked = [&](float ms, const DslashCfg& cfg) {
-    return fusable && cfg.sp == 1 ? ms - kFusedCreditMs : ms;
-  };
+  const float credit = credit_applies(c) && c.fusable ? kFusedCreditMs : 0.f;
+  auto ranked = [&](float ms, const DslashCfg& cfg) { return cfg.sp == 1 ? ms - credit : ms; };
   float best_ms = 1e30f;
   int rc = LQCD_OK;
   std::vector<std::pair<float, DslashCfg>> timed;
@@ -397,8 +411,6 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
       rc = LQCD_ERR_HIP;
       break;
     }
-    ms = ranked(ms, cfg);
-    if (runs) timed.push_back({ms, cfg});
     if (runs && tuning_verbose())
       fprintf(stderr,
               "[lqcd tune] L=%dx%dx%dx%d prec=%d fmt=%d nrhs=%d mode=%d block=%d B=%d xcd=%d "
@@ -406,6 +418,8 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
               c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, t.prec, t.fmt, c.nrhs, t.mode, cfg.block,
               cfg.rhs_block, cfg.xcd, cfg.ty, cfg.tz, cfg.nt, cfg.occ, cfg.ilv, cfg.lf, cfg.hh,
               cfg.ns, cfg.tm, cfg.tp, cfg.sp, 1000.0 * ms);
+    ms = ranked(ms, cfg);
+    if (runs) timed.push_back({ms, cfg});
     if (runs && ms < best_ms) {
       best_ms = ms;
       best = cfg;
@@ -528,7 +542,8 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
             "xcd=%d ty=%d tz=%d nt=%d occ=%d ilv=%d lf=%d hh=%d ns=%d tm=%d tp=%d sp=%d (%.2f us)\n",
             c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, t.prec, t.fmt, c.nrhs, t.mode, best.block,
             best.rhs_block, best.xcd, best.ty, best.tz, best.nt, best.occ, best.ilv, best.lf,
-            best.hh, best.ns, best.tm, best.tp, best.sp, 1000.0 * best_ms);
+            best.hh, best.ns, best.tm, best.tp, best.sp,
+            1000.0 * (best_ms + (best.sp == 1 ? credit : 0.f)));
   *out = best;
   return LQCD_OK;
 }

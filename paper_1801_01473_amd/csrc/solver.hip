@@ -1376,15 +1376,19 @@ int read_flags(const Ctx& c, GlobalFlags* host) {
   return LQCD_OK;
 }
 
-// Whether the iteration computes its scalars inside the stencil and the update
-// (three launches) instead of in one-workgroup kernels between them (five): the
-// D_eo kernel must be the one that can, the partials must fit its one-pass
-// sum, and only the base direction may need a new coefficient in the update.
+// Whether the iteration may compute its scalars inside the stencil and the update
+// (three launches) instead of in one-workgroup kernels between them (five): only
+// the base direction may need a new coefficient in the update.
+bool fusable_scalars(const Core& k) {
+  return fused_scalars_enabled() && (k.win > 1 || k.nshift == 1);
+}
+
+// Whether it does: the D_eo kernel must be the one that can, and the partials must
+// fit its one-pass sum.
 bool fused_scalars(const Ctx& c, const Core& k, const Phase& ph) {
   const int nbv = (c.g.Vh + kVecBlock - 1) / kVecBlock;
   const int nb = std::max({ph.nb_oe, ph.nb_eo, nbv});
-  return ph.c_eo.sp == 1 && fused_scalars_enabled() && (k.win > 1 || k.nshift == 1) &&
-         fused_partials_pay(nb, k.nsys);
+  return ph.c_eo.sp == 1 && fusable_scalars(k) && fused_partials_pay(nb, k.nsys);
 }
 
 int tune_phase(const Ctx& c, const Core& k, Phase& ph) {
@@ -1394,6 +1398,7 @@ int tune_phase(const Ctx& c, const Core& k, Phase& ph) {
   if ((rc = dslash_tuned(t, c.p.rhs_block, c.s, &ph.c_oe))) return rc;
   t.out_par = 0;
   t.mode = DM_CG;
+  t.fusable = fusable_scalars(k) ? 1 : 0;
   if ((rc = dslash_tuned(t, c.p.rhs_block, c.s, &ph.c_eo))) return rc;
   ph.nb_oe = dslash_nblocks(c.g, ph.c_oe);
   ph.nb_eo = dslash_nblocks(c.g, ph.c_eo);
