@@ -1347,7 +1347,8 @@ bool debug_enabled() {
   return e && e[0] == '1';
 }
 
-// LQCD_DEBUG=1: print the scalars of every system (synchronises the stream).
+// LQCD_DEBUG=1: print the scalars of every system (synchronises the stream); tune_phase
+// prints which kernels a phase runs.
 void debug_dump(const Ctx& c, const Core& k, const char* where) {
   if (!debug_enabled()) return;
   std::vector<SysState> h(k.nsys);
@@ -1403,6 +1404,10 @@ int tune_phase(const Ctx& c, const Core& k, Phase& ph) {
   ph.nb_oe = dslash_nblocks(c.g, ph.c_oe);
   ph.nb_eo = dslash_nblocks(c.g, ph.c_eo);
   ph.fused = fused_scalars(c, k, ph);
+  if (debug_enabled())
+    fprintf(stderr, "[lqcd debug] phase %s n=%d pairs=%d: D_oe sp=%d, D_eo sp=%d B=%d, fused=%d\n",
+            ph.prec == LQCD_F32 ? "f32" : "f64", k.nsys, ph.pairs, ph.c_oe.sp, ph.c_eo.sp,
+            ph.c_eo.rhs_block, ph.fused ? 1 : 0);
   return LQCD_OK;
 }
 
