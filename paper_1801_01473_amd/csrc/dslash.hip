@@ -123,7 +123,7 @@ constexpr int kSplitOncePerRhsVh = 1 << 16;
 constexpr float kFusedCreditMs = 0.006f;
 
 bool credit_applies(const DslashCall& c) {
-  return c.mode == DM_CG && fused_partials_pay((c.g.Vh + 63) / 64, c.nrhs);
+  return c.mode == DM_CG && fused_partials_pay((c.g.Vh + 63) / 64, c.nrhs, c.pairs != 0);
 }
 
 // A CG update that the credit would apply to, of a solve that cannot use it: tuned

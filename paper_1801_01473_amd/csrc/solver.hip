@@ -1389,7 +1389,7 @@ bool fusable_scalars(const Core& k) {
 bool fused_scalars(const Ctx& c, const Core& k, const Phase& ph) {
   const int nbv = (c.g.Vh + kVecBlock - 1) / kVecBlock;
   const int nb = std::max({ph.nb_oe, ph.nb_eo, nbv});
-  return ph.c_eo.sp == 1 && fusable_scalars(k) && fused_partials_pay(nb, k.nsys);
+  return ph.c_eo.sp == 1 && fusable_scalars(k) && fused_partials_pay(nb, k.nsys, ph.pairs != 0);
 }
 
 int tune_phase(const Ctx& c, const Core& k, Phase& ph) {

@@ -12,13 +12,20 @@ namespace lqcd {
 constexpr int kFusedPartials = 2 * kScalarThreads;
 
 // Whether that pays: nb workgroups a right-hand side then read nb partials each
-// from L2, nb^2 nrhs doubles in all and twice that for the step length.  CG and
-// mixed multi-shift, ms, without and with: 20^4 (nb 1250) 13.6 and 12.3, with two
-// right-hand sides 15.2 and 14.2; 22^3 x 24 (1997) 17.7 and 15.9; but 24 x 20^2 x
-// 26 (1950) with two 18.3 and 19.7, 16^3 x 30 (960) with four 16.1 and 17.9, 16^4
-// (512) with eight 15.4 and 16.8, with four 12.3 and 12.1.
-inline bool fused_partials_pay(int64_t nb, int nrhs) {
-  return nb <= kFusedPartials && nb * nb * nrhs <= (int64_t(1) << (nrhs <= 2 ? 22 : 20));
+// from L2, nb^2 nrhs doubles in all and twice that for the step length.  A whole
+// iteration with the scalars inside and in kernels of their own, us, 8 shifts:
+//   FP64, 1 system   8^4 18.0 22.8   16^4 29.3 37.2   22^3 x 24 (nb 1997) 69.7 76.5
+//   FP64, 2          16^4 36.1 41.8  20^4 (1250) 63.0 65.5; 22^3 x 24 loses
+//   FP64, 4          16^4 (512) 50.6 56.9; with 8: 12^3 x 24 (324) 58.0 60.8
+//   FP32, 1          16^4 22.7 27.7  22^3 x 24 42.8 46.2;   3: 16^4 36.2 38.8
+// In pairs a workgroup sums two systems' partials, four arrays, and the stencil
+// they hide behind is the shortest:
+//   2 systems  8^3 x 16 (64) 27.0 28.9  12^3 x 16 (216) 28.6 31.1  12^3 x 24 33.2 32.9
+//   4          8^4 (32) 28.5 29.8       12^2 x 8 x 16 (144) 33.4 33.1  16^4 47.0 43.0
+//   8          8^3 x 16 31.6 32.7       144 39.4 37.6  12^3 x 24 53.2 45.1
+inline bool fused_partials_pay(int64_t nb, int nrhs, bool pairs) {
+  const int64_t most = int64_t(1) << (pairs ? 17 : nrhs <= 2 ? 22 : 20);
+  return nb <= kFusedPartials && nb * nb * nrhs <= most;
 }
 
 // The sums of K arrays of n[k] <= kFusedPartials doubles by a workgroup of 256

@@ -60,3 +60,13 @@ def test_fused_where_the_comparisons_assume_it(lq, monkeypatch, capfd, L, n, blo
     monkeypatch.setenv("LQCD_FUSED_SCALARS", "0")
     assert all(ph[-1] == 0 for ph in phases(lq, capfd, L, n, mixed))
     assert all(ph[-1] == 0 for ph in phases(lq, capfd, L, n, mixed, single=True))
+
+
+@pytest.mark.parametrize("L,n,fused", [((8, 8, 8, 16), 2, 1), ((8, 8, 8, 16), 8, 1),
+                                       ((16, 16, 16, 16), 2, 0), ((12, 12, 12, 24), 8, 0)])
+def test_pairs_fuse_up_to_fewer_partials(lq, monkeypatch, capfd, L, n, fused):
+    """nb^2 n partials of 2^13, 2^15 and 2^19, 2^20; as separate rows up to 2^20."""
+    monkeypatch.setenv("LQCD_DSLASH_CFG", SPLIT % 2)
+    assert phases(lq, capfd, L, n, True)[1] == ("f32", 1, 1, 2, fused)
+    monkeypatch.setenv("LQCD_RHS_PAIRS", "0")
+    assert phases(lq, capfd, L, n, True)[1] == ("f32", 0, 1, 2, 1)
