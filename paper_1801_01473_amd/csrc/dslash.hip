@@ -109,13 +109,6 @@ constexpr int kTuneCacheFormat = 1;
 // Half volumes up to which the direction-split stencil is a candidate.
 constexpr int kSplitMaxVh = 1 << 18;
 
-// Half volumes up to which the plain modes try it with one right-hand side per
-// pass over the links although there are several.  The timings below repeat on
-// one link field, which larger lattices' callers may have moved out of the
-// 256 MB cache in between: 18 x 22 x 20 x 26, FP64, 3 right-hand sides, A x:
-// 55 us on one field but 74 on three in turn, against 57 and 67 in pairs.
-constexpr int kSplitOncePerRhsVh = 1 << 16;
-
 // What the split kernel saves elsewhere when the solve takes its scalars into the
 // CG kernels (DslashCall::fusable, fused_partials_pay): their one-workgroup kernels,
 // 5 and 4 us a launch at 16^4, against about 1 us more in the CG kernels each.  Its
@@ -305,8 +298,14 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     for (int b : {1, 2}) {
       if (forced ? b != forced : b > c.nrhs) continue;
       if (c.pairs && b == 1) continue;
-      if (b == 1 && c.nrhs > 1 && !forced && c.mode != DM_CG && c.g.Vh > kSplitOncePerRhsVh)
-        continue;
+      // One right-hand side a pass over the links when there are several pays only
+      // in the CG update, whose workgroups may each sum their systems' partials.
+      // A x, FP64, us with one and with two a pass, on one link field and (as a
+      // program with several fields has it) on fields past the last-level cache in
+      // turn: 16^4, 2 systems 17.8 18.2, 21.7 20.3; 4 systems 24.9 22.7, 30.7 26.1;
+      // 20^4, 3 systems 44.6 44.1, 55.7 51.7; FP32 16^4, 4 systems 16.6 14.4, 19.0 16.2.
+      // The timings below repeat on one field and would not tell.
+      if (b == 1 && c.nrhs > 1 && !forced && c.mode != DM_CG) continue;
       for (int x : {0, 1}) {
         DslashCfg v;
         v.block = 256;
