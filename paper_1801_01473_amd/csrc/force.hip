@@ -400,11 +400,17 @@ int lqcd_fermion_force(const lqcd_geom* g, const void* U64, int32_t npf, int32_t
   Alphas al{};
   for (int i = 0; i < nshift; ++i) al.a[i] = alpha[i];
   const unsigned grid = unsigned((k.Vh + 63) / 64);
-  // (y, z) tiles keep a site's +-z and +-t neighbours near in launch order: 32^4,
-  // 12 pairs, 422 us with 16 x 4 tiles, 440 with 8 x 4; 24^4, 48 pairs, 367 with
-  // 12 x 6, 372 with 8 x 6; but 48^4, 96 pairs, 10.65 ms with 8 x 6 tiles, 11.25
-  // with 16 x 6 (45 and 59 GB read), 32^3 x 48 3.04 and 3.07.
-  const bool large = k.Vh >= 3 << 18 && chunk_tile(k.Ly, 8) >= 4;
+  // (y, z) tiles keep a site's +-z and +-t neighbours near in launch order: 48^4, 96
+  // pairs, 12.1 ms without, 11.0 with 16 x 6 tiles (59 GB read), 10.4 with 8 x 6 (45).
+  // On large lattices tiles of eight rows, where they divide Ly, ms of 16 (else the
+  // next divisor) and 8:   12 pairs      48 pairs       96 pairs
+  //   32^3 x 48           0.601 0.592   1.612 1.592   2.992 2.968
+  //   32^3 x 64           0.866 0.841   2.169 2.164   4.028 4.001
+  //   40^4                0.992 0.980   2.672 2.662   5.012 4.989
+  //   48^4                2.030 2.018   5.591 5.535  11.006 10.423
+  // but 36^4 0.666 with 12 and 0.692 with 6 rows, 44^4 within 1 %, 32^3 x 40 0.510
+  // 0.513, and 24^4, 48 pairs, 0.367 with 12 and 0.372 with 8.
+  const bool large = k.Vh >= 3 << 18 && k.Ly % 8 == 0;
   const int ty = chunk_tile(k.Ly, large ? 8 : 16), tz = chunk_tile(k.Lz, 7);
   if (k.Vh <= kForceGroupsVh && npf * nshift >= 2)
     hipLaunchKernelGGL(k_force<2>, dim3(grid), dim3(2 * kForceBlock), 0, (hipStream_t)stream, k,
