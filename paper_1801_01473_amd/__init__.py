@@ -473,11 +473,8 @@ def _workspaces() -> _Workspaces:
 
 
 def _workspace(nbytes: int, device) -> torch.Tensor:
-    """At least nbytes for a call on the current stream: kept for the next ones, so
-    that iteration graphs find it at the same address.  A captured call gets memory
-    of the capture's own."""
-    if _capturing():
-        return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    """At least nbytes for a call on the current stream, not captured: kept for the
+    next ones, so that iteration graphs find it at the same address."""
     pool, key = _workspaces(), (device, _stream())
     ws = pool.get(key)
     if ws is None or ws.numel() < nbytes:
@@ -492,14 +489,27 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
     return ws
 
 
+# Twice a workspace is kept up to this size: asking torch for it costs the host a
+# microsecond or two, which calls on small lattices notice.
+_KEEP_TWICE = 64 << 20
+
+
 def _workspace_twice(nbytes: int, device) -> torch.Tensor:
-    """2 nbytes where that costs nothing that stays -- the kept workspace if it is
-    that large, else memory that goes back to torch's allocator with the call --
-    and the kept workspace of nbytes where so much is not there."""
-    ws = None if _capturing() else _workspaces().get((device, _stream()))
-    if ws is not None and ws.numel() >= 2 * nbytes:
-        return ws
+    """2 nbytes where that costs nothing that stays -- a small size, or the kept
+    workspace if it is that large, else memory that goes back to torch's allocator
+    with the call -- and nbytes where so much is not there.  A captured call gets
+    memory of the capture's own."""
+    if _capturing():
+        try:
+            return torch.empty(2 * nbytes, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            return torch.empty(nbytes, dtype=torch.uint8, device=device)
     try:
+        if 2 * nbytes <= _KEEP_TWICE:
+            return _workspace(2 * nbytes, device)
+        ws = _workspaces().get((device, _stream()))
+        if ws is not None and ws.numel() >= 2 * nbytes:
+            return ws
         return torch.empty(2 * nbytes, dtype=torch.uint8, device=device)
     except torch.OutOfMemoryError:
         return _workspace(nbytes, device)

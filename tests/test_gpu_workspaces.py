@@ -52,10 +52,12 @@ def test_captured(case):
         assert torch.equal(F, ref[0]) and torch.equal(other, ref[1])
 
 
-def test_force_where_twice_the_workspace_does_not_fit(case):
+@pytest.mark.parametrize("keep", [0, 1 << 40])
+def test_force_where_twice_the_workspace_does_not_fit(case, monkeypatch, keep):
     """With room for the required workspace only, the force is formed in two passes
     of three planes; nothing that it used is kept beyond that size."""
     lq, g, U, ref = case
+    monkeypatch.setattr(lq, "_KEEP_TWICE", keep)
     need = int(lq._fn("lqcd_gauge_force_staples_workspace_bytes")(g.c()))
     F = lq.empty_links(g)
     lq.release_workspace()

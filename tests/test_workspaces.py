@@ -66,6 +66,10 @@ def test_release_and_out_of_memory(stream, monkeypatch):
 def test_twice_the_size_is_not_kept(stream, monkeypatch):
     """Twice a size comes from the kept workspace or is given back; without the
     memory for it, the size itself."""
+    small = lq._workspace_twice(1000, CPU)
+    assert lq._workspace(2000, CPU).data_ptr() == small.data_ptr()
+    monkeypatch.setattr(lq, "_KEEP_TWICE", 0)
+    lq.release_workspace()
     ws = lq._workspace_twice(1000, CPU)
     assert ws.numel() == 2000 and not lq._workspaces()
     kept = lq._workspace(3000, CPU)
