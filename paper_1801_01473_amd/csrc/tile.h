@@ -61,36 +61,6 @@ __device__ __forceinline__ bool link_thread(const KGeom& g, int64_t idx, LinkThr
   return t.i < g.Vh;
 }
 
-// Thread order of the kernels whose work per site splits into `nt` tasks of
-// equal code (directions, planes): a wave takes 64 consecutive entries i of
-// the site order, one parity and one task, and the waves of a workgroup (and
-// the next workgroups of the same XCD) take the other tasks and the other
-// parity of the same 64 entries.  All tasks of a site read the links around
-// it, so they run while those are in one L2, and the sites in flight -- what
-// the L2 has to hold -- are the waves in flight divided by 2 nt.  Task and
-// parity are uniform over the wave (scalar registers).
-constexpr int kTaskBlock = 256;
-
-struct WaveTask {
-  int task, par, i;
-};
-
-inline unsigned task_blocks(int Vh, int nt) {
-  const int64_t waves = int64_t(2) * nt * ((Vh + 63) / 64);
-  return unsigned((waves + kTaskBlock / 64 - 1) / (kTaskBlock / 64));
-}
-
-__device__ __forceinline__ bool wave_task(const KGeom& g, int nt, WaveTask& t) {
-  const int w = __builtin_amdgcn_readfirstlane(xcd_block(blockIdx.x, gridDim.x, 1) *
-                                                   (kTaskBlock / 64) +
-                                               int(threadIdx.x >> 6));
-  const int chunk = w / (2 * nt), r = w - chunk * (2 * nt);
-  t.par = r / nt;
-  t.task = r - t.par * nt;
-  t.i = chunk * 64 + int(threadIdx.x & 63);
-  return t.i < g.Vh;
-}
-
 // Thread order of the kernels whose work at a site splits into a few tasks of
 // equal code (directions, planes): a workgroup takes 64 consecutive entries of
 // the site order at one parity, and its waves take the tasks, so that links
