@@ -366,8 +366,8 @@ def rhmc_trajectory_bench(lq, torch, g48, U48):
     (dH(20) / dH(40) ~ 4 for the second-order scheme) and the multi-step
     scheme (10 outer fermion steps, 4 gauge substeps each): time, dH and the
     accept decision.  Then the tree-level Symanzik gauge force kernel alone on
-    the workload lattice: 85 SU(3) products (198 flops each) per link when every
-    staple is multiplied out (the loop form executes about 29), against
+    the workload lattice: the 117 SU(3) products (198 flops each) a site that the
+    loop form executes -- 6 x 11 for the loops, 40 transports of 1.28 -- against
     the FP64 vector peak."""
     import synth
     L = (16, 16, 16, 16)
@@ -400,7 +400,7 @@ def rhmc_trajectory_bench(lq, torch, g48, U48):
         res[key] = (time.time() - t0, r)
     F = lq.empty_links(g48, lq.F64, lq.LINKS18, "cuda")
     ms = event_time_ms(lambda: lq.gauge_force(g48, U48, 5.0, out=F), 10)
-    flops = 8 * g48.Vh * 85 * 198
+    flops = 2 * g48.Vh * 117 * 198
     # stout smearing (one level) and its chain-rule step on the workload lattice
     chain = lq.stout_smear(g48, U48, 0.15)
     ms_smear = event_time_ms(lambda: lq.stout_smear(g48, U48, 0.15), 10)
