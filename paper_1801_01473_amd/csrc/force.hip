@@ -411,7 +411,11 @@ int lqcd_fermion_force(const lqcd_geom* g, const void* U64, int32_t npf, int32_t
   // but 36^4 0.666 with 12 and 0.692 with 6 rows, 44^4 within 1 %, 32^3 x 40 0.510
   // 0.513, and 24^4, 48 pairs, 0.367 with 12 and 0.372 with 8.
   const bool large = k.Vh >= 3 << 18 && k.Ly % 8 == 0;
-  const int ty = chunk_tile(k.Ly, large ? 8 : 16), tz = chunk_tile(k.Lz, 7);
+  const int rows = chunk_tile(k.Ly, large ? 8 : 16), tz = chunk_tile(k.Lz, 7);
+  // An odd number of rows, which Ly = 18, 22, 26, 30 have, loses 1 to 5 % against whole
+  // ones: 18^4 46.0 45.0 us with 12 pairs, 117.3 115.9 with 48; 22^4 101.1 99.7, 272.2
+  // 268.5; 30^4 348.8 336.1, 896.9 891.2 (even ones lose up to 4 %: 24^4 356 366).
+  const int ty = rows % 2 && k.Ly <= 30 ? k.Ly : rows;
   if (k.Vh <= kForceGroupsVh && npf * nshift >= 2)
     hipLaunchKernelGGL(k_force<2>, dim3(grid), dim3(2 * kForceBlock), 0, (hipStream_t)stream, k,
                        (const double2*)U64, (const double2*)X, npf, nshift, al, mode, accumulate,

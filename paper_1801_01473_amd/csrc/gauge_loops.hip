@@ -26,12 +26,12 @@
 // were stored as full matrices and 340 with every staple multiplied out, and
 // 2 launches instead of 12.  Both passes are bound by their memory path, not
 // by arithmetic (with the products taken out of a copy they took the same
-// time): pass 1 by HBM (3.1 GB of links read ~3 times through 4 MB L2s, 6.1 GB
-// written, 3.6 ms at 48^4), pass 2 by what misses L2 (60 % of its requests, 25 GB
-// at 6.5 TB/s: the sites in flight on an XCD have 9 MB of fields, links and
+// time): pass 1 by HBM (12.3 GB read past L2 for 3.1 GB of links, 6.1 GB written,
+// 3.6 ms at 48^4), pass 2 by what misses L2 (60 % of its requests, 24.3 GB at 6.4
+// TB/s, 3.8 ms: the sites in flight on an XCD have 9 MB of fields, links and
 // forces), so the links that the waves of a workgroup share go through LDS
 // (4.5 -> 3.7 ms).
-// 48^4: 25.6 ms with stored staples, 7.1 ms now.
+// 48^4: 25.7 ms with stored staples, 7.1 ms now (7.0 without the look at the links).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
