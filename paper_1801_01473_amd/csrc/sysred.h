@@ -190,7 +190,7 @@ __device__ __forceinline__ void store_beta(SysState& S, GlobalFlags* gf, int nsh
   const int s = threadIdx.x;
   if (s < 64) {  // one wavefront: its reads of the state come before its stores
     bool go = S.upd_any != 0;
-    const int wpos = S.wpos;
+    const int wpos = S.wpos, err = S.err;
     const bool bad = go && (!(rr == rr && fabs(rr) <= 1.7e308) || (wc && wpos >= ba.win));
     if (bad) go = false;
     const double rho = S.rho_k, a_step = S.a;
@@ -222,7 +222,7 @@ __device__ __forceinline__ void store_beta(SysState& S, GlobalFlags* gf, int nsh
         if (!ba.fused) S.upd_any = 0;
         gf->error = 1;
       }
-      if (S.err) {  // found here or by the step length
+      if (bad || err) {  // found here or by the step length
         S.done = 1;
         S.live = 0;
       }
