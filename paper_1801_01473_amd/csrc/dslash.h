@@ -61,6 +61,7 @@ struct DslashCall {
   // right-hand sides with one 16-byte access (same arithmetic, same bits).
   int pairs = 0;
   double* partials = nullptr; // [nrhs][nblocks]
+  int solve = 0;    // tuning: part of a solve, run again and again on one link field
   int fusable = 0;  // tuning: the solve can take its scalars into the CG kernels
   // Step length inside the fused CG update (k_dslash_split only): when sys is
   // set, every workgroup sums the partials of |D_oe p|^2 (step_t, step_nt of

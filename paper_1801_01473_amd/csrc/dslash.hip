@@ -70,7 +70,7 @@ int dslash_launch(const DslashCall& c, const DslashCfg& cfg, hipStream_t st) {
 
 namespace {
 
-using TuneKey = std::tuple<int, int, int, int, int, int, int, int, int, int, int>;
+using TuneKey = std::tuple<int, int, int, int, int, int, int, int, int, int, std::string>;
 std::mutex g_tune_mu;
 std::map<TuneKey, DslashCfg> g_tune;
 
@@ -101,13 +101,24 @@ bool tuning_verbose() {
 // "<key>;<block>,<B>,<xcd>,<tz>,<nt>,<occ>,<ilv>,<lf>,<hh>,<ty>[,<ns>[,<tm>,<tp>[,<sp>]]]"
 // where the key names the cache format, the GPU architecture and CU count,
 // the geometry, precision, link format, RHS count, forced RHS block, mode,
-// pairs and, where it matters (separate_scalars), a solve whose scalars stay
-// in kernels of their own.  Lines that do not parse, or whose configuration is not valid for
+// pairs and, where it matters, the kind of caller (caller_kind).  Lines that do not parse, or whose configuration is not valid for
 // the shape, are ignored (that shape is tuned again).
 constexpr int kTuneCacheFormat = 1;
 
 // Half volumes up to which the direction-split stencil is a candidate.
 constexpr int kSplitMaxVh = 1 << 18;
+
+// Half volumes up to which the plain modes also try it with one right-hand side a
+// pass over the links when there are several: more workgroups, an eighth off a
+// launch on the smallest lattices (8^4, 2 systems 7.2 and 8.2 us), but the links are
+// read again for each.  On one link field that pays further up (FP64 D_oe, 16^4, 2
+// systems 12.4 13.5 us, 16^3 x 32 18.4 19.8, 18^4, 3 systems 19.0 20.9), and solves,
+// which run on one, try it everywhere (DslashCall::solve).  A program with fields past
+// the last-level cache in turn loses by it from there on, which the timings below on
+// one field would not tell: A x, FP64, 12^4, 3 systems 12.7 14.2 us; 16^4, 2 systems
+// 21.7 20.3, 4 systems 30.7 26.1; 20^4, 3 systems 55.7 51.7; FP32 16^4, 4 systems
+// 19.0 16.2.
+constexpr int kSplitOncePerRhsVh = 1 << 14;
 
 // What the split kernel saves elsewhere when the solve takes its scalars into the
 // CG kernels (DslashCall::fusable, fused_partials_pay): their one-workgroup kernels,
@@ -120,16 +131,23 @@ bool credit_applies(const DslashCall& c) {
   return c.mode == DM_CG && fused_partials_pay((c.g.Vh + 63) / 64, c.nrhs, c.pairs != 0);
 }
 
-// A CG update that the credit would apply to, of a solve that cannot use it: tuned
-// and kept apart from those that can.
-bool separate_scalars(const DslashCall& c) { return credit_applies(c) && !c.fusable; }
+constexpr char kSeparate[] = "/sep", kSolve[] = "/solve";
+
+// Callers that get a choice of their own, tuned and kept apart: CG updates that the
+// credit would apply to but whose solve cannot use it, and D_oe of a solve where a
+// plain call does not try all that it does.
+std::string caller_kind(const DslashCall& c, int forced) {
+  if (credit_applies(c) && !c.fusable) return kSeparate;
+  if (c.solve && c.mode == DM_PLAIN && c.nrhs > 1 && !c.pairs && !forced &&
+      c.g.Vh > kSplitOncePerRhsVh && c.g.Vh <= kSplitMaxVh)
+    return kSolve;
+  return "";
+}
 
 const char* tune_cache_path() {
   const char* e = std::getenv("LQCD_TUNE_CACHE");
   return (e && e[0]) ? e : nullptr;
 }
-
-constexpr char kSeparateSuffix[] = "/sep";
 
 std::string tune_cache_key(const DslashCall& c, int forced) {
   int dev = 0;
@@ -146,7 +164,7 @@ std::string tune_cache_key(const DslashCall& c, int forced) {
   std::snprintf(buf, sizeof(buf), "v%d/%s/%dcu/%dx%dx%dx%d/p%d/f%d/n%d/b%d/m%d%s%s",
                 kTuneCacheFormat, arch.c_str(), cus, c.g.Lx, c.g.Ly, c.g.Lz, c.g.Lt, c.prec, c.fmt,
                 c.nrhs, forced, c.mode, c.pairs ? "/pairs" : "",
-                separate_scalars(c) ? kSeparateSuffix : "");
+                caller_kind(c, forced).c_str());
   return buf;
 }
 
@@ -170,8 +188,9 @@ bool tune_cache_lookup(const char* path, const std::string& key, const DslashCal
                        DslashCfg* out) {
   FILE* f = std::fopen(path, "r");
   if (!f) return false;
-  const bool sep = separate_scalars(c);
-  const std::string with_credit = sep ? key.substr(0, key.size() - std::strlen(kSeparateSuffix)) : key;
+  const std::string with_credit = caller_kind(c, forced) == kSeparate
+                                      ? key.substr(0, key.size() - std::strlen(kSeparate))
+                                      : key;
   char line[512];
   bool found = false;
   while (std::fgets(line, sizeof(line), f)) {
@@ -240,7 +259,7 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     }
   }
   const TuneKey key{c.g.Lx, c.g.Ly, c.g.Lz,  c.g.Lt, c.prec, c.fmt,
-                    c.nrhs, forced, c.mode, c.pairs, separate_scalars(c) ? 1 : 0};
+                    c.nrhs, forced, c.mode, c.pairs, caller_kind(c, forced)};
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(key);
@@ -299,14 +318,9 @@ int dslash_tuned(const DslashCall& c, int forced, hipStream_t st, DslashCfg* out
     for (int b : {1, 2}) {
       if (forced ? b != forced : b > c.nrhs) continue;
       if (c.pairs && b == 1) continue;
-      // One right-hand side a pass over the links when there are several pays only
-      // in the CG update, whose workgroups may each sum their systems' partials.
-      // A x, FP64, us with one and with two a pass, on one link field and (as a
-      // program with several fields has it) on fields past the last-level cache in
-      // turn: 16^4, 2 systems 17.8 18.2, 21.7 20.3; 4 systems 24.9 22.7, 30.7 26.1;
-      // 20^4, 3 systems 44.6 44.1, 55.7 51.7; FP32 16^4, 4 systems 16.6 14.4, 19.0 16.2.
-      // The timings below repeat on one field and would not tell.
-      if (b == 1 && c.nrhs > 1 && !forced && c.mode != DM_CG) continue;
+      if (b == 1 && c.nrhs > 1 && !forced && c.mode != DM_CG && !c.solve &&
+          c.g.Vh > kSplitOncePerRhsVh)
+        continue;
       for (int x : {0, 1}) {
         DslashCfg v;
         v.block = 256;

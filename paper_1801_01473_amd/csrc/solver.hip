@@ -1406,6 +1406,7 @@ int tune_phase(const Ctx& c, const Core& k, Phase& ph) {
   int rc;
   DslashCall t = phase_call(c, k, ph, 1);
   t.pairs = ph.pairs;
+  t.solve = 1;
   if ((rc = dslash_tuned(t, c.p.rhs_block, c.s, &ph.c_oe))) return rc;
   t.out_par = 0;
   t.mode = DM_CG;
